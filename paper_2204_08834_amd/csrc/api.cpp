@@ -408,6 +408,7 @@ struct Group {
     std::shared_ptr<DevBuf> S32;       // FP32 spectra, one per member
     std::shared_ptr<DevBuf> P32;       // refinement: FP32 first iterates, one per member
     std::shared_ptr<DevBuf> partials;  // per-workgroup partial sums, part_stride per member
+    bool plane = false;                // planes small enough for k_plane.hip (both transforms at once)
     int npart = 0;                     // workgroups of the forward x pass (upper bound)
     int part_stride = 0;               // doubles of partials per member
     Tune tune;                         // launch variants of this shape (autotuned)
@@ -429,13 +430,16 @@ struct PassStat {
 // One pass of one shape group, recorded instead of launched (work-list
 // schedule): the launches of every group at the same position of their
 // sequences are issued together, one work-list launch per pass kind.
-enum RecKind { RK_XF, RK_XR, RK_XI, RK_Y, RK_Z, RK_RC, RK_SUM };
+// RK_NONE holds the place of a y pass that a plane pass includes, so that the
+// groups' sequences stay aligned.
+enum RecKind { RK_XF, RK_XR, RK_XI, RK_PF, RK_PI, RK_Y, RK_Z, RK_RC, RK_SUM, RK_NONE };
 struct Rec {
     int kind = RK_XF;
     std::string name;
     double bytes = 0.0;
     XFwdArgs xf{};
     XInvArgs xi{};
+    const void *twy = nullptr;  // plane passes: the table along y
     YArgs y{};
     ZArgs z{};
     SumSeg sum{};
@@ -657,6 +661,8 @@ int build_group(Group &g, Alloc &A)
     if ((rc = A.put(t.lamx, lx.data(), lx.size() * 8))) return rc;
     if ((rc = A.put(t.lamy, ly.data(), ly.size() * 8))) return rc;
     if ((rc = A.put(t.lamz, lz.data(), lz.size() * 8))) return rc;
+    g.plane = d.bc_x == POISSON_BC_PERIODIC && d.bc_y == POISSON_BC_PERIODIC &&
+              plane_fits(internal_prec(d.precision), d.nx, d.ny);
     const size_t n = g.members.size();
     g.npart = x_fwd_blocks(internal_prec(d.precision), d.nx, d.ny, d.nz, 0, 0);
     g.part_stride = partial_slots(d) * 4;
@@ -755,6 +761,11 @@ int kr_group(const LSet &L)
     return L.p->list_mode ? L.p->count : (int)L.g->members.size();
 }
 
+// Both transforms of a plane by one workgroup: plain input, small planes.
+// With per-pass timing the transforms along x and y run (and are timed) as
+// passes of their own.
+bool use_plane(const LSet &L) { return L.g->plane && !L.p->timing; }
+
 int pass_x_fwd(LSet &L, bool residual, bool want_partials, bool sum = true)
 {
     Group &g = *L.g;
@@ -808,15 +819,25 @@ int pass_x_fwd(LSet &L, bool residual, bool want_partials, bool sum = true)
     }
     int np = 0;
     int rc;
+    const bool plane = !residual && !div && use_plane(L);
+    const void *twy = g.tab.twy[L.prec == P_F32 ? 1 : 0]->p;
+    if (plane) {
+        np = g.d.nz;  // one record per plane
+        bytes = (double)g.N * (8.0 + sb) * L.n;
+    }
     if (L.p->rec) {
         Rec r;
-        r.kind = residual ? RK_XR : RK_XF;
+        r.kind = residual ? RK_XR : (plane ? RK_PF : RK_XF);
         r.name = name;
         r.bytes = bytes;
         r.xf = a;
+        r.twy = twy;
         L.p->rec->push_back(r);
-        np = x_fwd_list_blocks(L.prec, a);
+        if (!plane) np = x_fwd_list_blocks(L.prec, a);
         rc = np < 0 ? hip_fail(name, -1) : POISSON_OK;
+    } else if (plane) {
+        rc = timed(L.p, name, bytes,
+                   [&] { return launch_plane_fwd(L.prec, PlaneFwd{a, twy}, L.p->ls); });
     } else {
         rc = timed(L.p, name, bytes, [&] { return launch_x_fwd(L.prec, a, &np, L.p->ls); });
     }
@@ -982,9 +1003,12 @@ int pass_z(LSet &L)
     return timed(L.p, name, bytes, [&] { return launch_z_periodic(L.prec, a, L.p->ls); });
 }
 
+// inverse pass along x, with the inverse y pass included where planes fit
 int pass_x_inv(LSet &L, bool accumulate)
 {
     Group &g = *L.g;
+    const bool plane = use_plane(L);
+    const void *twy = g.tab.twy[L.prec == P_F32 ? 1 : 0]->p;
     // the inverse x pass follows the inverse y pass, which wrote the planes in order
     XInvArgs a{L.dev, L.n, L.one.S, L.one.p, g.tab.twx[L.prec == P_F32 ? 1 : 0]->p, g.d.nx,
                g.d.ny, g.d.nz, accumulate ? 1 : 0, g.tune.rev, nullptr,
@@ -1006,11 +1030,15 @@ int pass_x_inv(LSet &L, bool accumulate)
     int rc = POISSON_OK;
     if (L.p->rec) {
         Rec r;
-        r.kind = RK_XI;
+        r.kind = plane ? RK_PI : RK_XI;
         r.name = name;
         r.bytes = bytes;
         r.xi = a;
+        r.twy = twy;
         L.p->rec->push_back(r);
+    } else if (plane) {
+        rc = timed(L.p, name, bytes,
+                   [&] { return launch_plane_inv(L.prec, PlaneInv{a, twy}, L.p->ls); });
     } else {
         rc = timed(L.p, name, bytes, [&] { return launch_x_inv(L.prec, a, L.p->ls); });
     }
@@ -1018,23 +1046,36 @@ int pass_x_inv(LSet &L, bool accumulate)
     return rc;
 }
 
+// a y pass that the plane pass before or after it includes
+int no_y(LSet &L)
+{
+    if (L.p->rec) {
+        Rec r;
+        r.kind = RK_NONE;
+        L.p->rec->push_back(r);
+    }
+    return POISSON_OK;
+}
+
 // transform of the right-hand side (or residual), z solve, inverse transform
 int solve_passes(LSet &L, bool accumulate_into_p, bool want_partials)
 {
     int rc;
+    const bool plane = use_plane(L);
     if ((rc = pass_x_fwd(L, false, want_partials))) return rc;
-    if ((rc = pass_y(L, false))) return rc;
+    // the projection's first pass transforms along x only
+    if ((rc = plane && !L.p->projecting ? no_y(L) : pass_y(L, false))) return rc;
     if ((rc = pass_z(L))) return rc;
-    if ((rc = pass_y(L, true))) return rc;
+    if ((rc = plane ? no_y(L) : pass_y(L, true))) return rc;
     return pass_x_inv(L, accumulate_into_p);
 }
 
 int correction_passes(LSet &L)
 {
     int rc;
-    if ((rc = pass_y(L, false))) return rc;
+    if ((rc = pass_y(L, false))) return rc;  // the residual pass transforms along x only
     if ((rc = pass_z(L))) return rc;
-    if ((rc = pass_y(L, true))) return rc;
+    if ((rc = use_plane(L) ? no_y(L) : pass_y(L, true))) return rc;
     return pass_x_inv(L, true);
 }
 
@@ -1071,6 +1112,20 @@ int issue_recs(poisson_plan p, std::vector<std::vector<Rec>> &per)
                 for (int k = 0; k < n; ++k) a[k] = rs[k]->xi;
                 rc = timed(p, name, bytes,
                            [&] { return launch_x_inv_list(prec, a.data(), n, p->ls); });
+                break;
+            }
+            case RK_PF: {
+                std::vector<PlaneFwd> a(n);
+                for (int k = 0; k < n; ++k) a[k] = PlaneFwd{rs[k]->xf, rs[k]->twy};
+                rc = timed(p, name, bytes,
+                           [&] { return launch_plane_fwd_list(prec, a.data(), n, p->ls); });
+                break;
+            }
+            case RK_PI: {
+                std::vector<PlaneInv> a(n);
+                for (int k = 0; k < n; ++k) a[k] = PlaneInv{rs[k]->xi, rs[k]->twy};
+                rc = timed(p, name, bytes,
+                           [&] { return launch_plane_inv_list(prec, a.data(), n, p->ls); });
                 break;
             }
             case RK_Y: {
@@ -1686,7 +1741,7 @@ int autotune_group(poisson_plan p, Group &g)
     // last-level cache
     auto whole = [&] { return solve_passes(L, false, false); };
     if (g.d.bc_z != POISSON_BC_PERIODIC) pick(g.tune.zv, 4, whole);
-    if (g.d.ny >= 64) pick(g.tune.yv, g.d.bc_y == POISSON_BC_PERIODIC ? 4 : 2, whole);
+    if (g.d.ny >= 64 && !g.plane) pick(g.tune.yv, g.d.bc_y == POISSON_BC_PERIODIC ? 4 : 2, whole);
     pick(g.tune.rev, 2, whole);
     if (p->precision == POISSON_FP32_REFINE) {
         // plane-range depths of the residual pass with transform and of the

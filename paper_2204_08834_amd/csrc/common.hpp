@@ -226,6 +226,36 @@ struct YArgs {
     const void *tw4;        // walls: exp(-i pi k/(2 ny)), k in [0, ny)
 };
 
+// Both transforms of whole planes (k_plane.hip): the x pass's arguments and
+// the table exp(-2 pi i t/ny).
+struct PlaneFwd {
+    XFwdArgs x;
+    const void *twy;
+};
+struct PlaneInv {
+    XInvArgs x;
+    const void *twy;
+};
+// radix passes of length n = 2^a or 3*2^a in the order of make_rplan
+__device__ __forceinline__ void plane_radices(int n, int &n8, int &n4, int &n2, int &n3)
+{
+    const int a = __ffs(n) - 1;
+    n3 = (n >> a) == 3 ? 1 : 0;
+    n8 = a / 3;
+    n4 = 0;
+    n2 = 0;
+    if (a % 3 == 2) {
+        n4 = 1;
+    } else if (a % 3 == 1) {
+        if (n8 > 0) {
+            n8 -= 1;
+            n4 = 2;
+        } else {
+            n2 = 1;
+        }
+    }
+}
+
 // z solve, walls (tridiagonal per (m, ky)) or periodic (transform along z).
 struct ZArgs {
     const ProbPtrs *batch;
@@ -324,6 +354,14 @@ __device__ __forceinline__ bool list_find(const PK_KARG ListArgs<A> *L, int &g, 
 int launch_x_fwd(int prec, const XFwdArgs &a, int *nblocks_out, hipStream_t s);
 int launch_x_inv(int prec, const XInvArgs &a, hipStream_t s);
 int launch_y(int prec, const YArgs &a, hipStream_t s);
+// x and y together, one workgroup per plane (periodic x and y, plain input):
+// planes that fit a workgroup's LDS only.  The forward pass writes one
+// partial record per plane.
+bool plane_fits(int prec, int nx, int ny);
+int launch_plane_fwd(int prec, const PlaneFwd &a, hipStream_t s);
+int launch_plane_inv(int prec, const PlaneInv &a, hipStream_t s);
+int launch_plane_fwd_list(int prec, const PlaneFwd *a, int n, hipStream_t s);
+int launch_plane_inv_list(int prec, const PlaneInv *a, int n, hipStream_t s);
 int launch_z_walls(int prec, const ZArgs &a, hipStream_t s);
 int launch_z_periodic(int prec, const ZArgs &a, hipStream_t s);
 // number of workgroups the forward x pass uses (size of its partials array);

@@ -31,6 +31,37 @@ int launch_x_inv_list_f32(const XInvArgs *, int, hipStream_t);
 int launch_x_inv_list_f64(const XInvArgs *, int, hipStream_t);
 int x_fwd_list_blocks_f32(const XFwdArgs &);
 int x_fwd_list_blocks_f64(const XFwdArgs &);
+int launch_plane_fwd_f32(const PlaneFwd &, hipStream_t);
+int launch_plane_fwd_f64(const PlaneFwd &, hipStream_t);
+int launch_plane_inv_f32(const PlaneInv &, hipStream_t);
+int launch_plane_inv_f64(const PlaneInv &, hipStream_t);
+int launch_plane_fwd_list_f32(const PlaneFwd *, int, hipStream_t);
+int launch_plane_fwd_list_f64(const PlaneFwd *, int, hipStream_t);
+int launch_plane_inv_list_f32(const PlaneInv *, int, hipStream_t);
+int launch_plane_inv_list_f64(const PlaneInv *, int, hipStream_t);
+bool plane_fits_f32(int, int);
+bool plane_fits_f64(int, int);
+
+bool plane_fits(int prec, int nx, int ny)
+{
+    return prec == P_F32 ? plane_fits_f32(nx, ny) : plane_fits_f64(nx, ny);
+}
+int launch_plane_fwd(int prec, const PlaneFwd &a, hipStream_t s)
+{
+    return prec == P_F32 ? launch_plane_fwd_f32(a, s) : launch_plane_fwd_f64(a, s);
+}
+int launch_plane_inv(int prec, const PlaneInv &a, hipStream_t s)
+{
+    return prec == P_F32 ? launch_plane_inv_f32(a, s) : launch_plane_inv_f64(a, s);
+}
+int launch_plane_fwd_list(int prec, const PlaneFwd *a, int n, hipStream_t s)
+{
+    return prec == P_F32 ? launch_plane_fwd_list_f32(a, n, s) : launch_plane_fwd_list_f64(a, n, s);
+}
+int launch_plane_inv_list(int prec, const PlaneInv *a, int n, hipStream_t s)
+{
+    return prec == P_F32 ? launch_plane_inv_list_f32(a, n, s) : launch_plane_inv_list_f64(a, n, s);
+}
 
 int launch_y_list(int prec, const YArgs *a, int n, hipStream_t s)
 {

@@ -7,6 +7,11 @@
     X(256) X(384) X(512) X(768) X(1024)
 #define PK_LENGTHS(X) PK_X_LENGTHS(X) X(1536) X(2048)
 
+// rows of nx = 2M whose planes may be transformed by one workgroup: two or
+// more radix passes of M, and an even number of butterflies in the pass that
+// splits (or merges) the half spectrum
+#define PK_PLANE_LENGTHS(X) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128)
+
 #define PK_CAT2(a, b) a##_##b
 #define PK_CAT(a, b) PK_CAT2(a, b)
 #ifdef PK_TAG
