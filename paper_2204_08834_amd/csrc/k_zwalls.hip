@@ -49,10 +49,7 @@
 // every column m holds two real x-modes (2m, 2m+1) as A + iB, so every column
 // takes this path (eigenvalues lam_x(2m), lam_x(2m+1)).  The singular column
 // (m, ky) = (0, 0) -- the zero wavenumber -- is solved in FP64 whatever the
-// precision: its right-hand side mean is removed (this removes mean(f), which
-// is reported), p is pinned by the zero-mean gauge, and the Neumann problem
-// p[k-1] - 2p[k] + p[k+1] = g[k] is integrated twice (face fluxes are the
-// running sums of g, p the running sums of the fluxes), then made zero-mean.
+// precision, by a workgroup of its own (z_zero_column).
 #include "fft_core.hpp"
 #include "lengths.hpp"
 
@@ -96,12 +93,154 @@ __device__ __forceinline__ size_t zw_slot(int f, int cc, int w, int C, int W)
     return (((size_t)(f / P) * C + cc) * W + w) * P + (f % P);
 }
 
+// Kernel arguments used from the start, asked for together: left to the
+// point of use, each 64-byte line of the argument block is a miss of its own
+// on the way to the first load of the fields.
+__device__ __forceinline__ void z_args_early(const ZArgs &a)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" ::"s"(a.batch), "s"(a.S), "s"(a.lamx), "s"(a.lamy), "s"(a.M), "s"(a.ny),
+                 "s"(a.nz), "s"(a.nx), "s"(a.dz2), "s"(a.inv_nxny), "s"(a.reverse), "s"(a.gate),
+                 "s"(a.dirichlet_z), "s"(a.regular), "s"(a.ywall), "s"(a.xwall));
+#endif
+}
+
+// Sum over a wavefront, and the sum over the lanes before this one.
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+__device__ __forceinline__ double wave_before(double v, int lane)
+{
+    double inc = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double o = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += o;
+    }
+    const double ex = __shfl_up(inc, 1, 64);
+    return lane == 0 ? 0.0 : ex;
+}
+
+// The singular column (m, ky) = (0, 0), in FP64 whatever the precision, by
+// the first wavefront of a workgroup of its own.  Its real part (the zero
+// x-mode; the imaginary part is the x-mode packed beside it and belongs to
+// the two-mode columns) is read in rows of 4 per lane, 256 rows at a time.
+// The mean of the right-hand side is removed (this removes mean(f), which is
+// reported) and the Neumann problem p[k-1] - 2p[k] + p[k+1] = g[k] is
+// integrated twice: face fluxes F are the running sums of g, p the running
+// sums of the fluxes; then p is made zero-mean.  Stretched z: the mean and
+// the gauge are volume-weighted, g_k = h_k (raw_k - mean) / (nx ny), and p
+// advances by the flux times the centre distance.
+// Solved inside the workgroup of the two-mode columns, its rows re-read one
+// at a time in five places, it was the longest chain of the pass: 12.1 us
+// against 8.8 for the same 32^3 grid without a zero mode (FP64).
+template <bool STR>
+__device__ __forceinline__ void z_zero_column(R *S_, const double *zrow, double *mean_out, int nz,
+                                           size_t stride, double scale, double inv_nxny,
+                                           double inv_ntot, double hsum)
+{
+    const int lane = threadIdx.x;
+    if (lane >= 64) return;
+    constexpr int Q = 4, SEG = 64 * Q;
+    PK_GLOBAL R *col = gbl(S_);
+    const int nseg = (nz + SEG - 1) / SEG;
+    double raw[Q], wt[Q], dc[Q], p[Q];
+    auto load = [&](int sg) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int k = sg * SEG + lane * Q + i;
+            const int kc = k < nz ? k : nz - 1;
+            raw[i] = double(col[(size_t)kc * stride]);
+            wt[i] = k >= nz ? 0.0 : (STR ? zrow[8 * kc + 2] : 1.0);
+            dc[i] = STR ? zrow[8 * kc + 4] : 1.0;
+        }
+    };
+    double tot = 0.0;
+    for (int sg = 0; sg < nseg; ++sg) {
+        load(sg);
+        tot += wt[0] * raw[0] + wt[1] * raw[1] + wt[2] * raw[2] + wt[3] * raw[3];
+    }
+    tot = wave_sum(tot);
+    const double mu = STR ? tot / hsum : tot / nz;
+    if (lane == 0 && mean_out) *mean_out = STR ? mu * inv_nxny : tot * inv_ntot;
+
+    double flux = 0.0, pos = 0.0;  // F below the segment, p of its first row
+    auto sweep = [&](int sg) {     // p of the lane's rows, up to a constant
+        if (nseg > 1) load(sg);
+        double f[Q], run = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            run += wt[i] * ((raw[i] - mu) * (STR ? inv_nxny : scale));
+            f[i] = run;
+        }
+        const double f0 = flux + wave_before(run, lane);
+        flux = __shfl(f0 + run, 63, 64);
+        run = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            p[i] = run;
+            run += (f0 + f[i]) * dc[i];
+        }
+        const double p0 = pos + wave_before(run, lane);
+        pos = __shfl(p0 + run, 63, 64);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) p[i] += p0;
+    };
+    double sx = 0.0;
+    for (int sg = 0; sg < nseg; ++sg) {
+        sweep(sg);
+        sx += wt[0] * p[0] + wt[1] * p[1] + wt[2] * p[2] + wt[3] * p[3];
+    }
+    sx = wave_sum(sx);
+    const double mean = STR ? sx / hsum : sx / nz;
+    flux = pos = 0.0;
+    for (int sg = 0; sg < nseg; ++sg) {
+        if (nseg > 1) sweep(sg);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int k = sg * SEG + lane * Q + i;
+            if (k < nz) col[(size_t)k * stride] = R(p[i] - mean);
+        }
+    }
+}
+
+// L rows of a column from its chunk's first row, `rows` of them in the grid
+// (the rest zero).  All loads are issued before the first is used: in the
+// two-mode columns a row's value goes to the other lane half at once, and
+// loaded one by one the rows' latencies added up (half of the pass at 32^3).
+// Where every lane of the wavefront has a whole chunk no row is tested.  Idle
+// lanes load a column of the grid that they do not use.
+template <int L, class V>
+__device__ __forceinline__ void zw_load(V (&d)[L], const PK_GLOBAL V *col, size_t plane, int rows)
+{
+    if (__all(rows >= L)) {
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            const PK_GLOBAL V &v = col[(size_t)i * plane];
+            d[i] = V{v.re, v.im};
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            d[i] = V{0, 0};
+            if (i < rows) {
+                const PK_GLOBAL V &v = col[(size_t)i * plane];
+                d[i] = V{v.re, v.im};
+            }
+        }
+    }
+}
+
 // One workgroup's work (block vb.x of problem vb.y): C chunks of L rows of W
 // columns; `smem_d` holds the dynamic LDS of zw_lds_bytes().
 template <int L, int W, bool STR = false> struct ZWBody {
     static __device__ __forceinline__ void run(const ZArgs &a0, VBlock vb, int C, int nspecial,
                                                double *smem_d)
     {
+        z_args_early(a0);
         if (gated_off(a0.batch, a0.gate, vb.y)) return;
         ZArgs a = a0;
         if (a.batch) {
@@ -109,9 +248,20 @@ template <int L, int W, bool STR = false> struct ZWBody {
             a.S = pq.S;
             if (a.zero_mean_out) a.zero_mean_out = pq.scal;
         }
+        // the first block takes the zero wavenumber
+        int bx = vb.x, gx = vb.gx;
+        if (!a.regular) {
+            if (bx == 0) {
+                z_zero_column<STR>((R *)a.S, a.zrow, a.zero_mean_out, a.nz,
+                                   2 * (size_t)a.ny * a.M, a.dz2 * a.inv_nxny, a.inv_nxny,
+                                   a.inv_ntot, a.hsum);
+                return;
+            }
+            bx -= 1;
+            gx -= 1;
+        }
         // C*W slots of 4 reals in lane-contiguous groups (zw_slot)
         R *buf = (R *)smem_d;
-        double *zbuf = smem_d + ((C * W * 4 * sizeof(R) + 7) / 8);  // 3*C doubles
 
         const int t = threadIdx.x;
         const int w = t % W, c = t / W;
@@ -121,8 +271,7 @@ template <int L, int W, bool STR = false> struct ZWBody {
         const size_t plane = (size_t)ny * M;
         PK_GLOBAL Cx<R> *S = gbl((Cx<R> *)a.S);
         const int s = c * L;
-        const int e = (s + L < nz) ? s + L : nz;  // chunk rows [s, e)
-        const bool special = vb.x < nspecial;
+        const bool special = bx < nspecial;
         const double scale = a.dz2 * a.inv_nxny;
         // stretched z: the rows' coefficients from the table (ZArgs::zrow); s of
         // the column is -(lam_x + lam_y) times dz^2 (uniform rows, divided by
@@ -136,7 +285,7 @@ template <int L, int W, bool STR = false> struct ZWBody {
         // FP64 keeps the cached global reads: the staged form needs more
         // registers than its 16-row chunks leave, 338 against 292 us)
         constexpr bool ZSTAGE = STR && sizeof(R) == 4;
-        R *ztab = (R *)(zbuf + 3 * C);
+        R *ztab = (R *)(smem_d + ((C * W * 4 * sizeof(R) + 7) / 8));
         if constexpr (ZSTAGE) {
             for (int i = t; i < C * L; i += W * C)
 #pragma unroll
@@ -147,24 +296,24 @@ template <int L, int W, bool STR = false> struct ZWBody {
 
         Cx<R> d[L];
         bool active;
-        bool zero_lane = false;
+        bool zero_col = false;
         int q = 0, ky = 0, kyn = 0, part = 0, mm = 0;
         double s_d;  // s = -(lam_x + lam_y) dz^2 >= 0
         if (!special) {
-            q = block_order(vb.x - nspecial, vb.gx - nspecial, a.reverse) * W + w;
+            q = block_order(bx - nspecial, gx - nspecial, a.reverse) * W + w;
+            const bool in = q < ny * M;
+            q = in ? q : 0;
             const int m = q % M;
             ky = q / M;
-            active = (q < ny * M) && (m != 0);
-            s_d = active ? -(a.lamx[m] + a.lamy[ky]) * sfac : 1.0;
-            const PK_GLOBAL Cx<R> *col = S + (size_t)s * plane + (active ? q : 0);
-#pragma unroll
-            for (int i = 0; i < L; ++i)
-                if (active && s + i < nz) {
-                    const PK_GLOBAL Cx<R> &v = col[(size_t)i * plane];
-                    d[i] = Cx<R>{v.re, v.im};
-                } else {
-                    d[i] = Cx<R>{R(0), R(0)};
-                }
+            active = in && m != 0;
+            if constexpr (sizeof(R) == 8) {
+                const double lx = a.lamx[m], ly = a.lamy[ky];
+                zw_load<L>(d, S + (size_t)s * plane + q, plane, nz - s);
+                s_d = active ? -(lx + ly) * sfac : 1.0;
+            } else {
+                s_d = active ? -(a.lamx[m] + a.lamy[ky]) * sfac : 1.0;
+                zw_load<L>(d, S + (size_t)s * plane + q, plane, active ? nz - s : 0);
+            }
         } else {
             // two-mode columns: lanes [0, W/2) take part A, lanes [W/2, W) part B
             // of the same (m, ky pair), so each half reads a contiguous run of m
@@ -172,7 +321,7 @@ template <int L, int W, bool STR = false> struct ZWBody {
             constexpr int H = W / 2 > 0 ? W / 2 : 1;
             part = w >= H ? 1 : 0;
             const int mi = w - part * H;
-            const int sb = vb.x;
+            const int sb = bx;
             const int mblk = a.xwall ? (M + H - 1) / H : 1;
             const int pair = a.xwall ? sb / mblk : sb * H + mi;
             mm = a.xwall ? (sb % mblk) * H + mi : 0;
@@ -188,21 +337,18 @@ template <int L, int W, bool STR = false> struct ZWBody {
                 ky = active ? pair : 0;
                 kyn = (ny - ky) % ny;
             }
-            zero_lane = active && mm == 0 && pair == 0 && part == 0 && !a.regular;
-            const double lx = a.xwall ? a.lamx[2 * (active ? mm : 0) + part]
-                                      : (part ? a.lamx[M] : a.lamx[0]);
-            s_d = (active && !zero_lane) ? -(lx + a.lamy[ky]) * sfac : 1.0;
+            // the zero wavenumber is part A of this column: its real part is
+            // the first block's
+            zero_col = active && mm == 0 && pair == 0 && !a.regular;
+            const int mc = active ? mm : 0;
+            const double lx = a.lamx[a.xwall ? 2 * mc + part : (part ? M : 0)], ly = a.lamy[ky];
             // part A reads column ky, part B column -ky (the same with walls along y)
-            const PK_GLOBAL Cx<R> *col =
-                S + (size_t)s * plane + (size_t)(part ? kyn : ky) * M + (active ? mm : 0);
+            zw_load<L>(d, S + (size_t)s * plane + (size_t)(part ? kyn : ky) * M + mc, plane,
+                       nz - s);
+            s_d = (active && !(zero_col && part == 0)) ? -(lx + ly) * sfac : 1.0;
 #pragma unroll
             for (int i = 0; i < L; ++i) {
-                const int k = s + i;
-                Cx<R> own = {R(0), R(0)};
-                if (active && k < nz) {
-                    const Cx<R> g = col[(size_t)i * plane];
-                    own = {g.re, g.im};
-                }
+                const Cx<R> own = {zero_col ? R(0) : d[i].re, d[i].im};
                 Cx<R> v;
                 if (a.ywall) {
                     v = part ? Cx<R>{own.im, R(0)} : Cx<R>{own.re, R(0)};
@@ -212,16 +358,14 @@ template <int L, int W, bool STR = false> struct ZWBody {
                     const Cx<R> z2 = cconj(part ? own : oth);    // conj Z(-ky)
                     v = part ? cscale(cmul_mi(csub(z1, z2)), R(0.5)) : cscale(cadd(z1, z2), R(0.5));
                 }
-                d[i] = (active && k < nz) ? v : Cx<R>{R(0), R(0)};
+                d[i] = v;
             }
         }
-#pragma unroll
-        for (int i = 0; i < L; ++i)
-            d[i] = cscale(d[i], R(STR ? zr(s + i, 2) * a.inv_nxny : scale));
-
-        // zero wavenumber: raw A(0,k) = Re S[k,0,0] is re-read (L1-resident)
-        // whenever needed, so the FP64 path keeps only scalars across barriers
-        auto zraw = [&](int k) -> double { return double(S[(size_t)k * plane].re); };
+        // the rows are scaled where phase 2 takes them: their loads stay in
+        // flight during phase 1 and its scan
+        auto rhs = [&](int i) -> Cx<R> {
+            return cscale(d[i], R(STR ? zr(s + i, 2) * a.inv_nxny : scale));
+        };
 
         const R sv = R(s_d);
         const R mw = rcp_nr(R(1) + sv);  // Moebius matrix [[1, s], [1, 1+s]] / (1+s)
@@ -257,11 +401,6 @@ template <int L, int W, bool STR = false> struct ZWBody {
             p00 = n00; p01 = n01; p10 = n10; p11 = n11;
         }
         sl(0, c) = p00; sl(1, c) = p01; sl(2, c) = p10; sl(3, c) = p11;
-        if (zero_lane) {
-            double zsum = 0.0;
-            for (int k = s; k < e; ++k) zsum += (STR ? zr(k, 2) : 1.0) * zraw(k);
-            zbuf[c] = zsum;
-        }
         __syncthreads();  // S1
 
         // v entering the chunk: apply the preceding chunks' maps to v (all
@@ -284,28 +423,6 @@ template <int L, int W, bool STR = false> struct ZWBody {
                 vprev0 = (sl(0, cc) * vprev0 + sl(1, cc)) * rcp_nr(sl(2, cc) * vprev0 + sl(3, cc));
         }
 
-        // zero wavenumber, FP64: g = (raw - mean raw) * scale; face fluxes
-        // F_k = sum_{j<=k} g_j; positions p_k = sum_{j<k} F_j (p_0 = 0)
-        double zmu = 0.0, zF0 = 0.0, zsF = 0.0;
-        if (zero_lane) {
-            double tot = 0.0, pre = 0.0;
-            for (int cc = 0; cc < C; ++cc) {
-                if (cc == c) pre = tot;
-                tot += zbuf[cc];
-            }
-            // stretched: the volume-weighted mean, g_k = h_k (raw_k - mean) / (nx ny),
-            // and positions advance by the flux times the centre distance
-            zmu = STR ? tot / a.hsum : tot / nz;
-            if (c == 0 && a.zero_mean_out)
-                *a.zero_mean_out = STR ? zmu * a.inv_nxny : tot * a.inv_ntot;
-            zF0 = STR ? (pre - zr(s, 5) * zmu) * a.inv_nxny
-                      : (pre - s * zmu) * scale;  // flux entering the chunk, F_{s-1}
-            double run = zF0;
-            for (int k = s; k < e; ++k) {
-                run += STR ? zr(k, 2) * (zraw(k) - zmu) * a.inv_nxny : (zraw(k) - zmu) * scale;
-                zsF += STR ? run * zr(k, 4) : run;
-            }
-        }
         __syncthreads();  // S2: Moebius slots consumed
 
         // ---- phase 2: local forward elimination ------------------------------
@@ -328,7 +445,7 @@ template <int L, int W, bool STR = false> struct ZWBody {
                     const R ex = sv * zt(k, 2) + zt(k, 3) + ak * vprev;
                     const R wv = rcp_nr(ck + ex);
                     const R vnew = ck > R(0) ? ex * wv : R(1);
-                    Dp = cscale(csub(cscale(Dp, ak), d[i]), wv);
+                    Dp = cscale(csub(cscale(Dp, ak), rhs(i)), wv);
                     Gp = ak * wv * Gp;
                     vk[i] = wv;
                     d[i] = Dp;
@@ -341,7 +458,7 @@ template <int L, int W, bool STR = false> struct ZWBody {
                         (nz == 1) ? sv + dir2 + dir2 : (k == nz - 1 ? ex + dir2 : R(1) + ex);
                     const R u = rcp_nr(piv);
                     const R vnew = last ? R(1) : ex * u;
-                    Dp = cscale(csub(Dp, d[i]), u);
+                    Dp = cscale(csub(Dp, rhs(i)), u);
                     Gp = u * Gp;
                     if (k == nz - 1) ulast = u;
                     vk[i] = vnew;
@@ -351,7 +468,6 @@ template <int L, int W, bool STR = false> struct ZWBody {
             }
             sl(0, c) = Dp.re; sl(1, c) = Dp.im; sl(2, c) = Gp;
         }
-        if (zero_lane) zbuf[C + c] = zsF;
         __syncthreads();  // S3
 
         {
@@ -394,19 +510,8 @@ template <int L, int W, bool STR = false> struct ZWBody {
             d[i] = X;
             Xn = X;
         }
-        double zP0 = 0.0, zsx = 0.0;
-        if (zero_lane) {
-            for (int cc = 0; cc < c; ++cc) zP0 += zbuf[C + cc];  // p_s
-            double run = zF0, xk = zP0;
-            for (int k = s; k < e; ++k) {
-                zsx += STR ? zr(k, 2) * xk : xk;
-                run += STR ? zr(k, 2) * (zraw(k) - zmu) * a.inv_nxny : (zraw(k) - zmu) * scale;
-                xk += STR ? run * zr(k, 4) : run;
-            }
-        }
         __syncthreads();  // S4: slots consumed
         sl(0, c) = Xn.re; sl(1, c) = Xn.im; sl(2, c) = Hn;
-        if (zero_lane) zbuf[2 * C + c] = zsx;
         __syncthreads();  // S5
 
         {
@@ -429,23 +534,6 @@ template <int L, int W, bool STR = false> struct ZWBody {
                 d[i] = {d[i].re + Hr * y.re, d[i].im + Hr * y.im};
             }
         }
-        if (zero_lane) {
-            double tot = 0.0;
-            for (int cc = 0; cc < C; ++cc) tot += zbuf[2 * C + cc];
-            const double mean = STR ? tot / a.hsum : tot / nz;
-            double run = zF0, xk = zP0;
-#pragma unroll
-            for (int i = 0; i < L; ++i) {
-                const int k = s + i;
-                if (k < nz) {
-                    d[i] = {R(xk - mean), R(0)};
-                    run += STR ? zr(k, 2) * (zraw(k) - zmu) * a.inv_nxny : (zraw(k) - zmu) * scale;
-                    xk += STR ? run * zr(k, 4) : run;
-                }
-            }
-        }
-        __syncthreads();  // S6: every zero-lane re-read of column (0,0) is done
-
         // ---- store ------------------------------------------------------------
         if (!special) {
             if (active) {
@@ -466,7 +554,9 @@ template <int L, int W, bool STR = false> struct ZWBody {
                 const R oim = __shfl_xor(d[i].im, H, 64);
                 const int k = s + i;
                 if (active && k < nz) {
-                    if (part == 0) {
+                    if (part == 0 && zero_col) {
+                        col[(size_t)i * plane].im = ore;  // B alone
+                    } else if (part == 0) {
                         // column ky: A + iB
                         col[(size_t)i * plane] = {d[i].re - oim, d[i].im + ore};
                     } else if (kyn != ky) {
@@ -481,7 +571,7 @@ template <int L, int W, bool STR = false> struct ZWBody {
 
 template <int W> constexpr size_t zw_lds_bytes(int C)
 {
-    return ((C * W * 4 * sizeof(R) + 7) / 8) * 8 + 3 * C * sizeof(double);
+    return ((C * W * 4 * sizeof(R) + 7) / 8) * 8;
 }
 
 template <int L, int W, int MAXT, bool STR>
@@ -504,12 +594,14 @@ __global__ __launch_bounds__(MAXT) void k_z_walls(ZArgs a0, int C, int nspecial)
 // recurrences are serial chains of reciprocals; with one system per lane
 // the pass was bound by their latency (2.5 TB/s in FP64 at 512x512x256),
 // two independent chains per lane keep twice the bytes in flight per chain.
-// Column (0, 0) is the zero mode (FP64, as in k_z_walls): the first system
-// of the first lane.
+// Column (0, 0) is the zero mode (z_zero_column): the first system of the
+// first lane.
 constexpr int ZR_V = 2;
 
+// FP32 16-row chunks: four waves per SIMD (left alone they take 130 VGPRs,
+// two over, and run three: 113 against 101 us at 512x512x256)
 template <int L, int W, int MAXT, bool STR>
-__global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
+__global__ __launch_bounds__(MAXT, sizeof(R) == 4 && L == 16 ? 4 : 1) void k_z_walls_r(ZArgs a0, int C)
 {
     constexpr int V = ZR_V;
     using RV = typename std::conditional<sizeof(R) == 4, float2, double2>::type;
@@ -521,9 +613,19 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
         if (a.zero_mean_out) a.zero_mean_out = pq.scal;
     }
     extern __shared__ double smem_d[];
+    // the first block takes the zero wavenumber
+    int bx = blockIdx.x, gx = gridDim.x;
+    if (!a.regular) {
+        if (bx == 0) {
+            z_zero_column<STR>((R *)a.S, a.zrow, a.zero_mean_out, a.nz, (size_t)a.ny * a.nx,
+                               a.dz2 * a.inv_nxny, a.inv_nxny, a.inv_ntot, a.hsum);
+            return;
+        }
+        bx -= 1;
+        gx -= 1;
+    }
     // C*W slots of 4V reals, every field lane-contiguous (zw_slot)
     R *buf = (R *)smem_d;
-    double *zbuf = smem_d + ((C * W * 4 * V * sizeof(R) + 7) / 8);  // 3*C doubles
 
     const int t = threadIdx.x;
     const int w = t % W, c = t / W;
@@ -532,7 +634,6 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
     const size_t plane = (size_t)ny * nx;  // reals per z-plane
     PK_GLOBAL R *S = gbl((R *)a.S);
     const int s = c * L;
-    const int e = (s + L < nz) ? s + L : nz;  // chunk rows [s, e)
     const double scale = a.dz2 * a.inv_nxny;
     // stretched z: row coefficients from the table, s per row times h_k (as
     // in ZWBody)
@@ -541,7 +642,7 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
     const double sfac = STR ? 1.0 : a.dz2;
     // stretched rows staged in LDS in FP32 (as in ZWBody)
     constexpr bool ZSTAGE = STR && sizeof(R) == 4;
-    R *ztab = (R *)(zbuf + 3 * C);
+    R *ztab = (R *)(smem_d + ((C * W * 4 * V * sizeof(R) + 7) / 8));
     if constexpr (ZSTAGE) {
         for (int i = t; i < C * L; i += W * C)
 #pragma unroll
@@ -551,10 +652,10 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
     auto zt = [&](int k, int f) -> R { return ZSTAGE ? ztab[4 * k + f] : R(zr(k, f)); };
 
     // systems q0 + v, v < V, of row ky
-    const int q0 = (block_order((int)blockIdx.x, (int)gridDim.x, a.reverse) * W + w) * V;
+    const int q0 = (block_order(bx, gx, a.reverse) * W + w) * V;
     const int r0 = q0 % nx, ky = q0 / nx;
     const bool active = q0 < ny * nx;
-    const bool zero_lane = active && q0 == 0 && !a.regular;
+    const bool zero_lane = active && q0 == 0 && !a.regular;  // holds the zero mode beside mode 1
     const R dir2 = a.dirichlet_z ? R(2) : R(0);
     R sv[V], mw[V], mws[V], mws0[V];
 #pragma unroll
@@ -572,15 +673,18 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
         const PK_GLOBAL R *col = S + (size_t)s * plane + (active ? q0 : 0);
 #pragma unroll
         for (int i = 0; i < L; ++i) {
-            const R sc = R(STR ? zr(s + i, 2) * a.inv_nxny : scale);
             RV x{R(0), R(0)};
             if (active && s + i < nz) x = *(const PK_GLOBAL RV *)(col + (size_t)i * plane);
-            d[i][0] = x.x * sc;
-            d[i][1] = x.y * sc;
+            d[i][0] = x.x;
+            d[i][1] = x.y;
         }
     }
-    // zero wavenumber: raw values re-read (L1-resident) whenever needed
-    auto zraw = [&](int k) -> double { return double(S[(size_t)k * plane]); };
+
+    // scaled where phase 2 takes them (as in ZWBody); the zero mode has none
+    auto rhs = [&](int i, int v) -> R {
+        const R sc = R(STR ? zr(s + i, 2) * a.inv_nxny : scale);
+        return d[i][v] * (v == 0 && zero_lane ? R(0) : sc);
+    };
 
     // ---- phase 1: Moebius product of the chunk (v recurrence) -----------
     R p00[V], p01[V], p10[V], p11[V];
@@ -613,11 +717,6 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
     for (int v = 0; v < V; ++v) {
         sl(4 * v, c) = p00[v]; sl(4 * v + 1, c) = p01[v]; sl(4 * v + 2, c) = p10[v]; sl(4 * v + 3, c) = p11[v];
     }
-    if (zero_lane) {
-        double zsum = 0.0;
-        for (int k = s; k < e; ++k) zsum += (STR ? zr(k, 2) : 1.0) * zraw(k);
-        zbuf[c] = zsum;
-    }
     __syncthreads();  // S1
 
     R vprev0[V];
@@ -647,23 +746,6 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
         }
     }
 
-    double zmu = 0.0, zF0 = 0.0, zsF = 0.0;
-    if (zero_lane) {
-        double tot = 0.0, pre = 0.0;
-        for (int cc = 0; cc < C; ++cc) {
-            if (cc == c) pre = tot;
-            tot += zbuf[cc];
-        }
-        zmu = STR ? tot / a.hsum : tot / nz;
-        if (c == 0 && a.zero_mean_out)
-            *a.zero_mean_out = STR ? zmu * a.inv_nxny : tot * a.inv_ntot;
-        zF0 = STR ? (pre - zr(s, 5) * zmu) * a.inv_nxny : (pre - s * zmu) * scale;
-        double run = zF0;
-        for (int k = s; k < e; ++k) {
-            run += STR ? zr(k, 2) * (zraw(k) - zmu) * a.inv_nxny : (zraw(k) - zmu) * scale;
-            zsF += STR ? run * zr(k, 4) : run;
-        }
-    }
     __syncthreads();  // S2
 
     // ---- phase 2: local forward elimination ------------------------------
@@ -684,7 +766,7 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
                 const R ex = sv[v] * zt(k, 2) + zt(k, 3) + ak * vprev[v];
                 const R wv = rcp_nr(ck + ex);
                 const R vnew = ck > R(0) ? ex * wv : R(1);
-                Dp[v] = (ak * Dp[v] - d[i][v]) * wv;
+                Dp[v] = (ak * Dp[v] - rhs(i, v)) * wv;
                 Gp[v] = ak * wv * Gp[v];
                 vk[i][v] = wv;
                 d[i][v] = Dp[v];
@@ -695,7 +777,7 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
                 const R piv = (nz == 1) ? sv[v] + dir2 + dir2 : (k == nz - 1 ? ex + dir2 : R(1) + ex);
                 const R u = rcp_nr(piv);
                 const R vnew = last ? R(1) : ex * u;
-                Dp[v] = (Dp[v] - d[i][v]) * u;
+                Dp[v] = (Dp[v] - rhs(i, v)) * u;
                 Gp[v] = u * Gp[v];
                 if (k == nz - 1) ulast[v] = u;
                 vk[i][v] = vnew;
@@ -709,7 +791,6 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
         sl(4 * v, c) = Dp[v];
         sl(4 * v + 1, c) = Gp[v];
     }
-    if (zero_lane) zbuf[C + c] = zsF;
     __syncthreads();  // S3
 
     {
@@ -747,23 +828,12 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
             Xn[v] = X;
             Hn[v] *= uk;
         }
-    double zP0 = 0.0, zsx = 0.0;
-    if (zero_lane) {
-        for (int cc = 0; cc < c; ++cc) zP0 += zbuf[C + cc];
-        double run = zF0, xk = zP0;
-        for (int k = s; k < e; ++k) {
-            zsx += STR ? zr(k, 2) * xk : xk;
-            run += STR ? zr(k, 2) * (zraw(k) - zmu) * a.inv_nxny : (zraw(k) - zmu) * scale;
-            xk += STR ? run * zr(k, 4) : run;
-        }
-    }
     __syncthreads();  // S4
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         sl(4 * v, c) = Xn[v];
         sl(4 * v + 1, c) = Hn[v];
     }
-    if (zero_lane) zbuf[2 * C + c] = zsx;
     __syncthreads();  // S5
 
     {
@@ -784,28 +854,19 @@ __global__ __launch_bounds__(MAXT) void k_z_walls_r(ZArgs a0, int C)
                 d[i][v] = d[i][v] + Hr[v] * y[v];
             }
     }
-    if (zero_lane) {
-        double tot = 0.0;
-        for (int cc = 0; cc < C; ++cc) tot += zbuf[2 * C + cc];
-        const double mean = STR ? tot / a.hsum : tot / nz;
-        double run = zF0, xk = zP0;
-#pragma unroll
-        for (int i = 0; i < L; ++i) {
-            const int k = s + i;
-            if (k < nz) {
-                d[i][0] = R(xk - mean);
-                run += STR ? zr(k, 2) * (zraw(k) - zmu) * a.inv_nxny : (zraw(k) - zmu) * scale;
-                xk += STR ? run * zr(k, 4) : run;
-            }
-        }
-    }
-    __syncthreads();  // S6: every zero-lane re-read of column (0,0) is done
-
     if (active) {
         PK_GLOBAL R *col = S + (size_t)s * plane + q0;
 #pragma unroll
         for (int i = 0; i < L; ++i)
-            if (s + i < nz) *(PK_GLOBAL RV *)(col + (size_t)i * plane) = RV{d[i][0], d[i][1]};
+            if (s + i < nz) {
+                // one vector store (as a pair of scalars, each would become a
+                // store of its own: 242 against 209 us in FP64 at 512x512x256)
+                typedef R rv2 __attribute__((ext_vector_type(2)));
+                if (zero_lane)
+                    col[(size_t)i * plane + 1] = d[i][1];
+                else
+                    *(PK_GLOBAL rv2 *)(col + (size_t)i * plane) = rv2{d[i][0], d[i][1]};
+            }
     }
 }
 
@@ -820,8 +881,8 @@ static int run_zwr(const ZArgs &a, hipStream_t s)
     constexpr int MAXT = zwr_maxt<L>();
     const int C = (a.nz + L - 1) / L;
     if (C * W > MAXT || a.nx % ZR_V != 0) return -1;
-    const int nb = (a.ny * a.nx / ZR_V + W - 1) / W;
-    const size_t shm = ((C * W * 4 * ZR_V * sizeof(R) + 7) / 8) * 8 + 3 * C * sizeof(double) +
+    const int nb = (a.ny * a.nx / ZR_V + W - 1) / W + (a.regular ? 0 : 1);
+    const size_t shm = ((C * W * 4 * ZR_V * sizeof(R) + 7) / 8) * 8 +
                        (STR && sizeof(R) == 4 ? (size_t)C * L * 4 * sizeof(R) : 0);
     hipLaunchKernelGGL((k_z_walls_r<L, W, MAXT, STR>), dim3(nb, a.batch ? a.nbatch : 1),
                        dim3(W * C), shm, s, a, C);
@@ -837,9 +898,9 @@ static int run_zw(const ZArgs &a, hipStream_t s)
     constexpr int H = W / 2 > 0 ? W / 2 : 1;
     const int nspecial = a.xwall ? npairs * ((a.M + H - 1) / H) : (npairs + H - 1) / H;
     const int nmain = a.xwall ? 0 : (a.ny * a.M + W - 1) / W;
-    const size_t shm = ((C * W * 4 * sizeof(R) + 7) / 8) * 8 + 3 * C * sizeof(double) +
+    const size_t shm = ((C * W * 4 * sizeof(R) + 7) / 8) * 8 +
                        (STR && sizeof(R) == 4 ? (size_t)C * L * 4 * sizeof(R) : 0);
-    hipLaunchKernelGGL((k_z_walls<L, W, MAXT, STR>), dim3(nspecial + nmain, a.batch ? a.nbatch : 1),
+    hipLaunchKernelGGL((k_z_walls<L, W, MAXT, STR>), dim3(nspecial + nmain + (a.regular ? 0 : 1), a.batch ? a.nbatch : 1),
                        dim3(W * C), shm, s, a, C, nspecial);
     return (int)hipGetLastError();
 }
@@ -906,7 +967,7 @@ static bool z_list_class(const ZArgs &a, int &cls, int &nt, int &gx, int &C, int
         const int H = W / 2 > 0 ? W / 2 : 1;
         nspecial = a.xwall ? npairs * ((a.M + H - 1) / H) : (npairs + H - 1) / H;
         const int nmain = a.xwall ? 0 : (a.ny * a.M + W - 1) / W;
-        gx = nspecial + nmain;
+        gx = nspecial + nmain + (a.regular ? 0 : 1);
         lds = cls == 1 ? zw_lds_bytes<32>(C) : zw_lds_bytes<ZL_W2>(C);
         return true;
     }
