@@ -60,9 +60,14 @@ template <int M> struct PlaneTile {
 // loc(u, line, j) gives butterfly u's line and index, kof(j) = j mod ns, ld
 // and st move its values.  MIDSYNC: st overwrites what ld reads, so every
 // value is read before the barrier and written after it.
-template <int EPT, int RAD, bool MIDSYNC, class Loc, class Kof, class Ld, class St>
+// `loaded` runs once the loads are issued.
+struct Nothing {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <int EPT, int RAD, bool MIDSYNC, class Loc, class Kof, class Ld, class St, class Hook>
 __device__ __forceinline__ void plane_pass(int nbf, int nt, const Cx<R> *tw, int tws, int nj,
-                                           int ns, Loc &&loc, Kof &&kof, Ld &&ld, St &&st)
+                                           int ns, Loc &&loc, Kof &&kof, Ld &&ld, St &&st,
+                                           Hook &&loaded)
 {
     constexpr int PER = (EPT + RAD - 1) / RAD;
     Cx<R> v[PER][RAD];
@@ -76,6 +81,7 @@ __device__ __forceinline__ void plane_pass(int nbf, int nt, const Cx<R> *tw, int
             for (int r = 0; r < RAD; ++r) v[q][r] = ld(b, j + r * nj);
         }
     }
+    loaded();
     if (MIDSYNC) __syncthreads();
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -100,9 +106,9 @@ __device__ __forceinline__ void plane_pass(int nbf, int nt, const Cx<R> *tw, int
 // pass 0 reads through gl, the last pass writes through gs, the others work
 // in place.  GL_TILE: gl reads the tile; GS_TILE: gs writes it.  Each pass
 // ends with a barrier unless it is the last.
-template <int M, int EPT, bool GL_TILE, bool GS_TILE, class GL, class GS>
+template <int M, int EPT, bool GL_TILE, bool GS_TILE, class GL, class GS, class Hook>
 __device__ __forceinline__ void plane_columns(int n, int nt, const Cx<R> *tw, PlaneTile<M> tile,
-                                              GL &&gl, GS &&gs)
+                                              GL &&gl, GS &&gs, Hook &&loaded)
 {
     int n8, n4, n2, n3;
     plane_radices(n, n8, n4, n2, n3);
@@ -120,13 +126,13 @@ __device__ __forceinline__ void plane_columns(int n, int nt, const Cx<R> *tw, Pl
         const int nj = n / RAD, nbf = M * nj, tws = n / (ns * RAD);
         const bool first = p == 0, last = p == passes - 1;
         if (first && last)
-            plane_pass<EPT, RAD, true>(nbf, nt, tw, tws, nj, ns, loc, kof, gl, gs);
+            plane_pass<EPT, RAD, true>(nbf, nt, tw, tws, nj, ns, loc, kof, gl, gs, loaded);
         else if (first)
-            plane_pass<EPT, RAD, GL_TILE>(nbf, nt, tw, tws, nj, ns, loc, kof, gl, ts);
+            plane_pass<EPT, RAD, GL_TILE>(nbf, nt, tw, tws, nj, ns, loc, kof, gl, ts, loaded);
         else if (last)
-            plane_pass<EPT, RAD, GS_TILE>(nbf, nt, tw, tws, nj, ns, loc, kof, tl, gs);
+            plane_pass<EPT, RAD, GS_TILE>(nbf, nt, tw, tws, nj, ns, loc, kof, tl, gs, Nothing{});
         else
-            plane_pass<EPT, RAD, true>(nbf, nt, tw, tws, nj, ns, loc, kof, tl, ts);
+            plane_pass<EPT, RAD, true>(nbf, nt, tw, tws, nj, ns, loc, kof, tl, ts, Nothing{});
         if (!last) __syncthreads();
         ns *= RAD;
         ++p;
@@ -136,6 +142,34 @@ __device__ __forceinline__ void plane_columns(int n, int nt, const Cx<R> *tw, Pl
     for (int i = 0; i < n2; ++i) run(std::integral_constant<int, 2>{});
     for (int i = 0; i < n3; ++i) run(std::integral_constant<int, 3>{});
 }
+
+// The tables of both transforms, x entries then y entries.  A pass 0 needs
+// neither, so the first entries of each thread go to registers, ahead of the
+// field's loads, and to LDS while those are in flight (loaded and stored
+// first, the tables' latency came before the field's).
+template <int M> struct PlaneTables {
+    const Cx<R> *x, *y;
+    int n, nt;
+    Cx<R> v[2];
+    __device__ __forceinline__ Cx<R> entry(int i) const { return i < 2 * M ? x[i] : y[i - 2 * M]; }
+    __device__ __forceinline__ void fetch()
+    {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int i = threadIdx.x + k * nt;
+            v[k] = entry(i < n ? i : 0);
+        }
+    }
+    __device__ __forceinline__ void store(Cx<R> *lds) const
+    {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int i = threadIdx.x + k * nt;
+            if (i < n) lds[i] = v[k];
+        }
+        for (int i = threadIdx.x + 2 * nt; i < n; i += nt) lds[i] = entry(i);
+    }
+};
 
 // LDS of a plane of ny rows: the tile (also the scratch of the partial sums)
 // and the tables of both transforms
@@ -170,8 +204,9 @@ template <int M, int EPT> struct PFBody {
         PlaneTile<M> tile{(Cx<R> *)lds};
         Cx<R> *s_twx = (Cx<R> *)(lds + plane_tile_bytes<M>(ny));
         Cx<R> *s_twy = s_twx + NX;
-        load_table(s_twx, (const Cx<R> *)a.tw, NX, nt);
-        load_table(s_twy, (const Cx<R> *)p0.twy, ny, nt);
+        PlaneTables<M> tab{(const Cx<R> *)a.tw, (const Cx<R> *)p0.twy, NX + ny, nt, {}};
+        tab.fetch();
+        auto tables = [&]() { tab.store(s_twx); };
 
         const PK_GLOBAL double *gf = gbl(a.f) + (size_t)k * ny * NX;
         PK_GLOBAL Cx<R> *S = gbl((Cx<R> *)a.S) + (size_t)k * ny * M;
@@ -193,7 +228,7 @@ template <int M, int EPT> struct PFBody {
                 return {R(fv.x), R(fv.y)};
             };
             auto k0 = [](int) { return 0; };
-            plane_pass<EPT, RAD, false>(ny * NJ, nt, s_twx, 0, NJ, 1, loc, k0, gl, ts);
+            plane_pass<EPT, RAD, false>(ny * NJ, nt, s_twx, 0, NJ, 1, loc, k0, gl, ts, tables);
             __syncthreads();
         }
         auto mid = [&](auto pc) {
@@ -204,7 +239,7 @@ template <int M, int EPT> struct PFBody {
                 j = u % NJ;
             };
             auto kof = [](int j) { return j % NS; };
-            plane_pass<EPT, RAD, true>(ny * NJ, nt, s_twx, 2 * (M / (NS * RAD)), NJ, NS, loc, kof, tl, ts);
+            plane_pass<EPT, RAD, true>(ny * NJ, nt, s_twx, 2 * (M / (NS * RAD)), NJ, NS, loc, kof, tl, ts, Nothing{});
             __syncthreads();
         };
         static_assert(pl.count <= 4, "");
@@ -271,7 +306,7 @@ template <int M, int EPT> struct PFBody {
         // ---- y: down the columns, the last pass to HBM
         auto cl = [&](int b, int i) -> Cx<R> { return tile.at(i, b); };
         auto gs = [&](int b, int i, Cx<R> v) { put(S + i * M + b, v); };
-        plane_columns<M, EPT, true, false>(ny, nt, s_twy, tile, cl, gs);
+        plane_columns<M, EPT, true, false>(ny, nt, s_twy, tile, cl, gs, Nothing{});
 
         if (a.partials) {
             double z1 = 0.0, z2 = 0.0;
@@ -327,9 +362,9 @@ template <int M, int EPT, bool ACC, bool P32> struct PIBody {
         PlaneTile<M> tile{(Cx<R> *)lds};
         Cx<R> *s_twx = (Cx<R> *)(lds + plane_tile_bytes<M>(ny));
         Cx<R> *s_twy = s_twx + NX;
-        load_table(s_twx, (const Cx<R> *)a.tw, NX, nt);
-        load_table(s_twy, (const Cx<R> *)p0.twy, ny, nt);
-        __syncthreads();
+        PlaneTables<M> tab{(const Cx<R> *)a.tw, (const Cx<R> *)p0.twy, NX + ny, nt, {}};
+        tab.fetch();
+        auto tables = [&]() { tab.store(s_twx); };
         const PK_GLOBAL Cx<R> *S = gbl((const Cx<R> *)a.S) + (size_t)k * ny * M;
         // ---- y: conj(FFT(conj)) down the columns, into the tile
         auto gl = [&](int b, int i) -> Cx<R> {
@@ -337,7 +372,7 @@ template <int M, int EPT, bool ACC, bool P32> struct PIBody {
             return {v.re, -v.im};
         };
         auto cs = [&](int b, int i, Cx<R> v) { tile.at(i, b) = cconj(v); };
-        plane_columns<M, EPT, false, true>(ny, nt, s_twy, tile, gl, cs);
+        plane_columns<M, EPT, false, true>(ny, nt, s_twy, tile, gl, cs, tables);
         __syncthreads();
 
         // the FP32 first iterate, in the coalesced order of the final loop, in
@@ -431,7 +466,7 @@ template <int M, int EPT, bool ACC, bool P32> struct PIBody {
                 j = u % NJ;
             };
             auto kof = [](int j) { return j % NS; };
-            plane_pass<EPT, RAD, true>(ny * NJ, nt, s_twx, 2 * (M / (NS * RAD)), NJ, NS, loc, kof, tl, st);
+            plane_pass<EPT, RAD, true>(ny * NJ, nt, s_twx, 2 * (M / (NS * RAD)), NJ, NS, loc, kof, tl, st, Nothing{});
             if (sync_after) __syncthreads();
         };
         constexpr int LAST = pl.count - 1;
@@ -592,12 +627,15 @@ static int run_planes(const A *a, int n, Cls cls_of, Launch launch, Own own)
     int total = 0, nt = 0;
     auto flush = [&]() -> int {
         if (L.nseg == 0) return 0;
+        // one shape alone: its own kernel, compiled for one length (FP32
+        // inverse: 72 VGPRs against the list's 109)
+        const bool single = L.nseg == 1;
         L.start[L.nseg] = total;
-        launch(L, total, nt, lds);
+        if (!single) launch(L, total, nt, lds);
         L.nseg = 0;
         lds = 0;
         total = nt = 0;
-        return (int)hipGetLastError();
+        return single ? own(L.a[0]) : (int)hipGetLastError();
     };
     for (int i = 0; i < n; ++i) {
         const auto &x = a[i].x;
@@ -608,6 +646,13 @@ static int run_planes(const A *a, int n, Cls cls_of, Launch launch, Own own)
             const int e = own(a[i]);
             if (e) return e;
             continue;
+        }
+        // a launch gives all its workgroups the LDS of its largest plane: much
+        // smaller planes get a launch of their own, with more of them per
+        // compute unit
+        if (L.nseg > 0 && 5 * b < 3 * lds) {
+            const int e = flush();
+            if (e) return e;
         }
         const int g = L.nseg++;
         L.start[g] = total;
