@@ -270,15 +270,18 @@ struct Tune {
     bool tuned = false;  // chosen by timing (else the defaults below)
 };
 
-// Defaults from measurements on MI355X (512x512x256 and 1024x1024x512):
-// wide z tiles for FP64 up to 256 planes, narrow beyond; the reverse for FP32.
+// Defaults from measurements on MI355X: wide z tiles for FP64 up to 256 planes
+// (512x512x256 204 against 283 us), narrow beyond (256x256x500 101 against
+// 120).  FP32: narrow up to 256 planes, wide to 384 (1024x512x300 322 against
+// 420), narrow beyond, where a wide tile is one workgroup per compute unit
+// (256x256x500 56 against 80, 1024x1024x512 1213 against 1298).
 // POISSON_ZWALLS_VARIANT / POISSON_Y_VARIANT / POISSON_BLOCK_ORDER=forward
 // force a choice (measurements).
 Tune heuristic_tune(const poisson_desc_t &d)
 {
     Tune t;
     const bool f64 = d.precision == POISSON_FP64;
-    t.zv = f64 ? (d.nz <= 256 ? 2 : 0) : (d.nz <= 256 ? 0 : 2);
+    t.zv = f64 ? (d.nz <= 256 ? 2 : 0) : (d.nz > 256 && d.nz <= 384 ? 2 : 0);
     t.yv = 0;
     t.rev = 1;
     return t;
@@ -610,6 +613,27 @@ bool same_problem(const poisson_desc_t &a, const poisson_desc_t &b)
            a.dz == b.dz && a.bc_x == b.bc_x && a.bc_y == b.bc_y && a.bc_z == b.bc_z;
 }
 
+// z-planes per workgroup of the residual pass with transform (one problem, not
+// tuned): the depth whose workgroups fill the device's resident slots in the
+// fewest whole rounds with at most 24 planes each.  The plain depth of 8,
+// halved until there are 1024 workgroups, left the last round mostly empty or
+// took 4 planes where 11 fit: 256^3 69 -> 56 us, 512x256x64 40 -> 34,
+// 256x256x100 33 -> 29, 384x192x150 cavity 63 -> 58; 512x512x256, where 8
+// planes fill ten rounds, 219 and 218.
+int residual_depth(const poisson_desc_t &d, int plain)
+{
+    const int slots = x_res_slots(d.nx, d.bc_x != POISSON_BC_PERIODIC ? 1 : 0, 1);
+    const int njb = x_fwd_blocks(P_F32, d.nx, d.ny, d.nz, 1, -d.nz, 1);
+    if (slots < 1 || njb < 1) return plain;
+    for (long rounds = 1; rounds <= 64; ++rounds) {
+        const long ranges = slots * rounds / njb;
+        if (ranges < 1) continue;
+        const long kr = (d.nz + ranges - 1) / ranges;
+        if (kr <= 24) return (int)-kr;
+    }
+    return plain;
+}
+
 // Tables of the group in A (copied now, or staged in A's host image), then
 // the field-sized buffers
 int build_group(Group &g, Alloc &A)
@@ -673,6 +697,8 @@ int build_group(Group &g, Alloc &A)
     const bool refine = d.precision == POISSON_FP32_REFINE;
     if (refine && (rc = A.get(g.P32, (size_t)g.N * 4 * n))) return rc;
     g.tune = initial_tune(g.d, !g.hz.empty());
+    if (refine && n == 1 && !g.tune.tuned && !getenv("POISSON_MARCH_PLANES"))
+        g.tune.kr = residual_depth(d, g.tune.kr);
     return POISSON_OK;
 }
 
