@@ -50,10 +50,14 @@ template <typename R> struct Const;
 template <> struct Const<float> {
     static constexpr float rsqrt2 = 0.70710678118654752440f;
     static constexpr float sqrt3_2 = 0.86602540378443864676f;
+    static constexpr float cos_pi8 = 0.92387953251128675613f;
+    static constexpr float sin_pi8 = 0.38268343236508977173f;
 };
 template <> struct Const<double> {
     static constexpr double rsqrt2 = 0.70710678118654752440;
     static constexpr double sqrt3_2 = 0.86602540378443864676;
+    static constexpr double cos_pi8 = 0.92387953251128675613;
+    static constexpr double sin_pi8 = 0.38268343236508977173;
 };
 
 // ---------------------------------------------------------------------------
@@ -85,8 +89,19 @@ constexpr RPlan make_rplan(int n)
 
 // plan variant: 0 = the order above, 1 = the same radices in reverse order
 // (small radix first)
+// 2, 3 = three passes with a radix of 12 or 16 for lengths that take four
+// passes otherwise (the y transforms, YCfg)
 constexpr RPlan get_rplan(int n, int variant)
 {
+    if (variant >= 2) {
+        switch (n) {
+        case 384: return RPlan{3, {8, 4, 12}};
+        case 768: return RPlan{3, {8, 8, 12}};
+        case 1024: return variant == 2 ? RPlan{3, {16, 8, 8}} : RPlan{3, {8, 8, 16}};
+        case 2048: return RPlan{3, {16, 16, 8}};
+        default: break;
+        }
+    }
     RPlan p = make_rplan(n);
     if (variant == 1) {
         for (int i = 0; i < p.count / 2; ++i) {
@@ -177,6 +192,62 @@ template <typename R> struct Bfly<R, 8> {
         for (int k = 0; k < 4; ++k) {
             x[k] = cadd(e[k], o[k]);
             x[k + 4] = csub(e[k], o[k]);
+        }
+    }
+};
+
+// 12 = 3 x 4 with coprime factors: input 4 a + 3 b, output 4 c + 9 d (mod 12),
+// and no twiddles between the 3-point and the 4-point transforms
+template <typename R> struct Bfly<R, 12> {
+    static __device__ __forceinline__ void run(Cx<R> *x)
+    {
+        Cx<R> t[3][4];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) t[a][b] = x[(4 * a + 3 * b) % 12];
+            Bfly<R, 4>::run(t[a]);
+        }
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            Cx<R> u[3] = {t[0][d], t[1][d], t[2][d]};
+            Bfly<R, 3>::run(u);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) x[(4 * c + 9 * d) % 12] = u[c];
+        }
+    }
+};
+
+// 16 = 4 x 4: X[c + 4 d] = sum_b w16^(b c) w4^(b d) sum_a x[4 a + b] w4^(a c)
+template <typename R> struct Bfly<R, 16> {
+    static __device__ __forceinline__ void run(Cx<R> *x)
+    {
+        const R c1 = Const<R>::cos_pi8, s1 = Const<R>::sin_pi8, h = Const<R>::rsqrt2;
+        Cx<R> t[4][4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+#pragma unroll
+            for (int a = 0; a < 4; ++a) t[b][a] = x[4 * a + b];
+            Bfly<R, 4>::run(t[b]);
+        }
+        const Cx<R> w1 = {c1, -s1}, w3 = {s1, -c1};
+        auto w2 = [&](Cx<R> v) -> Cx<R> { return {h * (v.re + v.im), h * (v.im - v.re)}; };
+        auto w6 = [&](Cx<R> v) -> Cx<R> { return {h * (v.im - v.re), -h * (v.re + v.im)}; };
+        t[1][1] = cmul(t[1][1], w1);
+        t[1][2] = w2(t[1][2]);
+        t[1][3] = cmul(t[1][3], w3);
+        t[2][1] = w2(t[2][1]);
+        t[2][2] = cmul_mi(t[2][2]);
+        t[2][3] = w6(t[2][3]);
+        t[3][1] = cmul(t[3][1], w3);
+        t[3][2] = w6(t[3][2]);
+        t[3][3] = cmul(t[3][3], Cx<R>{-c1, s1});
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            Cx<R> u[4] = {t[0][c], t[1][c], t[2][c], t[3][c]};
+            Bfly<R, 4>::run(u);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) x[c + 4 * d] = u[d];
         }
     }
 };
@@ -338,8 +409,8 @@ __device__ __forceinline__ void fft_tile(const Cx<R> *__restrict__ tw, int tws, 
             if (b < NB) gstore(b, 0, v);
         }
     } else {
-        fft_passes<R, N, NB, NT, LF, PAD, GL_LDS, 0, make_rplan(N).count, PV>(tw, tws, gload,
-                                                                              gstore, tile);
+        fft_passes<R, N, NB, NT, LF, PAD, GL_LDS, 0, get_rplan(N, PV).count, PV>(tw, tws, gload,
+                                                                                 gstore, tile);
     }
 }
 

@@ -24,7 +24,15 @@ using R = PK_REAL;
 // Tile variants V (chosen per shape by the plan's autotuner):
 //   bit 0: 256-byte row segments (twice the x-wavenumbers per workgroup)
 //   bit 1: radix passes in reverse order (small radix first)
-template <int N, int V> struct YCfg {
+// Without bit 1, lengths of 384, 768, 1024 and 2048 take three passes (a
+// radix of 12 or 16 among them) instead of four: with one or two workgroups
+// per compute unit every LDS pass less shortens the pass (FP64, forward /
+// inverse, us: 384x384x200 105 / 127 -> 85 / 113, 768x768x100 209 / 245 ->
+// 192 / 229, 1024x1024x512 1900 / 1921 -> 1830 / 1884).  At 1024 the radix 16
+// goes first in the forward transform and last in the inverse, whose first
+// pass reads what the z solve left in HBM: with half of the threads loading
+// sixteen rows each it took 2325 us there.
+template <int N, int V, bool INV = false> struct YCfg {
     // 128-byte row segments: 16 complex floats or 8 complex doubles; the
     // tile (up to 128 KB at N = 1024) stays in one workgroup's LDS
     static constexpr int NB0 = (sizeof(R) == 4 ? 16 : 8) * ((V & 1) ? 2 : 1);
@@ -32,14 +40,14 @@ template <int N, int V> struct YCfg {
     static constexpr int NB = (NB0 * N <= MAXE) ? NB0 : ((MAXE / N) < 1 ? 1 : MAXE / N);
     static constexpr int NT = pick_nt(NB * N, sizeof(R) == 4 ? 16 : 8);
     static constexpr int PAD = (NB >= 8) ? 1 : 0;
-    static constexpr int PV = (V & 2) ? 1 : 0;
+    static constexpr int PV = (V & 2) ? 1 : (INV ? 3 : 2);
 };
 
 // One workgroup's work: block vb.x (tile of NB x-wavenumbers of one plane)
 // of problem vb.y; LDS carved from `lds` (LDS_BYTES).  Called by the
 // per-group kernel and by the work-list kernel.
 template <int N, bool INV, int V> struct YBody {
-    using C = YCfg<N, V>;
+    using C = YCfg<N, V, INV>;
     static constexpr int NB = C::NB, NT = C::NT;
     using Tile = LdsTile<R, N, NB, true, C::PAD>;
     static constexpr size_t TILE_B = sizeof(Cx<R>) * Tile::elems;
