@@ -182,8 +182,8 @@ int poisson_solve(poisson_plan plan, const double *rhs_dev, double *sol_dev,
  * message on stderr) before any work is enqueued.
  * State: the array keeps the last call's contents.  The tables are
  * regenerated and copied (then `stream` is synchronised once) only when the
- * descriptor differs from the previous call's on that GPU; the scalars are
- * cleared by a kernel on every call.  All calls on one GPU share the one
+ * descriptor differs from the previous call's on that GPU; everything else
+ * is written by a call before it reads it.  All calls on one GPU share the one
  * array: calls that overlap in time on one GPU (from several host threads,
  * or on several streams) race and give wrong results; serialise them.
  * Synchronisation otherwise as poisson_solve (FP32_REFINE synchronises once

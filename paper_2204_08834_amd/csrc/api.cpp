@@ -2167,10 +2167,8 @@ int solve_noalloc(const poisson_desc_t *d, void *stream, const double *rhs, doub
     }
     poisson_plan_s *p = D.plan.get();
     p->stream = s;
-    // the array keeps the previous call's contents: clear the scalars and
-    // control records (the other pieces are written before they are read)
-    const int e = launch_zero(p->scalars->p, state_bytes(1), s);
-    if (e) return hip_fail("scratch clear", e);
+    // the array keeps the previous call's contents: everything the host-driven
+    // solve reads from it (tables apart) it has written before
     return solve_all(p, &rhs, &sol, stats);
 }
 

@@ -184,6 +184,16 @@ template <int N> struct YWCfg {
     static constexpr bool FITS_NOPAD = LDS_CU / B_NOPAD == LDS_CU / B_GLB;
     static constexpr int PAD = FITS_PAD ? PAD0 : (FITS_NOPAD ? 0 : PAD0);
     static constexpr bool W4_LDS = FITS_PAD || FITS_NOPAD;
+    // radix plan, as YCfg: three passes at 384, 768 and 1024 (FP64, forward /
+    // inverse, us: 384x384x200 100 / 128 -> 84 / 113, 512x768x100 141 / 157 ->
+    // 139 / 144; FP32 512x1024x150 175 / 157 -> 166 / 148).  2048 keeps four (a
+    // first or last pass of radix-16 pairs does not fit the registers), and so
+    // does the FP64 forward pass at 1024 (388 us against 450 with 100 VGPRs)
+    static constexpr int pv(bool inv)
+    {
+        if (N == 2048 || (N == 1024 && sizeof(R) == 8 && !inv)) return 0;
+        return inv ? 3 : 2;
+    }
 };
 
 __device__ __forceinline__ int wall_reorder(int j, int n) { return 2 * j < n ? 2 * j : 2 * n - 1 - 2 * j; }
@@ -246,15 +256,15 @@ __global__ __launch_bounds__((YWCfg<N>::NT)) void k_yw(YArgs a0)
             return (sine && (r & 1)) ? Cx<R>{-v.re, -v.im} : Cx<R>{v.re, v.im};
         };
         auto lstore = [&](int b, int n, Cx<R> v) { out.at(b, n) = v; };
-        constexpr RPlan pl = make_rplan(N);
+        constexpr RPlan pl = get_rplan(N, C::pv(INV));
         constexpr int LR = pl.count >= 2 ? pl.r[pl.count - 1] : 1;
         if constexpr (pl.count >= 2 && (N / LR) % 2 == 0 && (WV & 1) == 0) {
             // every pass but the last into LDS; the last pass with butterfly
             // pairs (p, NJ - p) (or (0, NJ/2)), so that V[k] and V[N-k] meet in
             // one thread and the coefficients are stored from registers:
             //   C[k] = (w_k V[k] + conj(w_k) V[N-k]) / 2, likewise C[N-k]
-            fft_passes<R, N, NB, NT, true, C::PAD, false, 0, pl.count - 1, 0>(s_tw, 1, gload,
-                                                                              lstore, tile);
+            fft_passes<R, N, NB, NT, true, C::PAD, false, 0, pl.count - 1, C::pv(INV)>(
+                s_tw, 1, gload, lstore, tile);
             __syncthreads();
             constexpr int RAD = LR, NJ = N / LR, U = NJ / 2, NU = NB * U;
             constexpr int PER = (NU + NT - 1) / NT;
@@ -308,7 +318,7 @@ __global__ __launch_bounds__((YWCfg<N>::NT)) void k_yw(YArgs a0)
                 }
             }
         } else {
-            fft_tile<R, N, NB, NT, true, C::PAD, false>(s_tw, 1, gload, lstore, tile);
+            fft_tile<R, N, NB, NT, true, C::PAD, false, C::pv(INV)>(s_tw, 1, gload, lstore, tile);
             __syncthreads();
             for (int e = threadIdx.x; e < NB * N; e += NT) {
                 const int b = e % NB, kk = e / NB;
@@ -344,7 +354,7 @@ __global__ __launch_bounds__((YWCfg<N>::NT)) void k_yw(YArgs a0)
             const R sg = (sine && (r & 1)) ? R(-1) : R(1);
             put(base + (size_t)r * M + b, Cx<R>{sg * v.re, -sg * v.im});
         };
-        constexpr RPlan pl = make_rplan(N);
+        constexpr RPlan pl = get_rplan(N, C::pv(INV));
         constexpr int R0 = pl.count >= 2 ? pl.r[0] : 1;
         if constexpr (pl.count >= 2 && (N / R0) % 2 == 0) {
             // pass 0 with butterfly pairs (p, NJ - p) (or (0, NJ/2)): W[n] and
@@ -407,10 +417,10 @@ __global__ __launch_bounds__((YWCfg<N>::NT)) void k_yw(YArgs a0)
             }
             __syncthreads();
             auto gnone = [&](int, int) -> Cx<R> { return {R(0), R(0)}; };
-            fft_passes<R, N, NB, NT, true, C::PAD, false, 1, pl.count, 0>(s_tw, 1, gnone, gstore,
-                                                                          tile);
+            fft_passes<R, N, NB, NT, true, C::PAD, false, 1, pl.count, C::pv(INV)>(s_tw, 1, gnone,
+                                                                                   gstore, tile);
         } else {
-            fft_tile<R, N, NB, NT, true, C::PAD, false>(s_tw, 1, gload, gstore, tile);
+            fft_tile<R, N, NB, NT, true, C::PAD, false, C::pv(INV)>(s_tw, 1, gload, gstore, tile);
         }
     }
 }
