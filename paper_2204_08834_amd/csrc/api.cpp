@@ -839,6 +839,9 @@ int pass_x_fwd(LSet &L, bool residual, bool want_partials, bool sum = true)
         // projection: f = alpha D(u, v, w) evaluated on the fly (one problem)
         const auto &pj = L.p->proj;
         a.residual = 2;
+        // an untuned exact depth is residual_depth()'s, chosen for the residual
+        // pass; this march keeps the plain depth
+        if (!g.tune.tuned && g.tune.kr < 0) a.kr_max = 0;
         a.u = pj.u;
         a.v = pj.v;
         a.w = pj.w;
