@@ -301,7 +301,10 @@ int poisson_plan_describe(poisson_plan plan, char *buf, int len);
  * Per-pass timing (tracing).  When enabled, every kernel launch of a solve is
  * bracketed by hipEvents on the plan's stream; the accumulated time and the
  * algorithmic HBM bytes of each pass are read back with
- * poisson_plan_get_timing (which synchronises the stream).
+ * poisson_plan_get_timing (which synchronises the stream).  While it is
+ * enabled every pass is a launch of its own: z-planes small enough for one
+ * workgroup to transform along x and y in one launch take the separate x and
+ * y passes instead.
  */
 typedef struct {
     char name[40];           /* pass name, e.g. "x_r2c_f32" */

@@ -105,9 +105,8 @@ __device__ __forceinline__ void z_args_early(const ZArgs &a)
 #endif
 }
 
-// The sum over the lanes of the first wavefront before this one, and over all
-// of them (the last is lane `last`: a workgroup of one chunk of few columns
-// has less than 64 threads, and lanes that are not there are not read).
+// The sum over the lanes of the first wavefront before this one, and over the
+// lanes up to `last`.
 __device__ __forceinline__ double wave_before(double v, int lane)
 {
     double inc = v;
@@ -147,10 +146,13 @@ __device__ __forceinline__ void z_zero_column(R *S_, const double *zrow, double 
 {
     const int lane = threadIdx.x;
     if (lane >= 64) return;
-    const int last = blockDim.x < 64 ? (int)blockDim.x - 1 : 63;
     constexpr int Q = 4, SEG = 64 * Q;
     PK_GLOBAL R *col = gbl(S_);
     const int nseg = (nz + SEG - 1) / SEG;
+    // The lane of a segment's last row.  Totals are taken there: a workgroup
+    // of few columns and chunks has less than 64 threads, and the order of a
+    // total's additions must not depend on how many there are.
+    auto last = [&](int sg) { return ((nz - sg * SEG < SEG ? nz - sg * SEG : SEG) - 1) / Q; };
     double wt[Q], dc[Q], hs[Q], pre[Q], p[Q];
     double sum = 0.0, pos = 0.0;   // right-hand sides below the segment, p of its first row
     auto prefix = [&](int sg) {    // sums up to and with each of the lane's rows
@@ -167,7 +169,7 @@ __device__ __forceinline__ void z_zero_column(R *S_, const double *zrow, double 
             pre[i] = run;
         }
         const double below = sum + wave_before(run, lane);
-        sum = __shfl(below + run, last, 64);
+        sum = __shfl(below + run, last(sg), 64);
 #pragma unroll
         for (int i = 0; i < Q; ++i) pre[i] += below;
     };
@@ -184,7 +186,7 @@ __device__ __forceinline__ void z_zero_column(R *S_, const double *zrow, double 
             run += (pre[i] - hs[i] * mu) * (STR ? inv_nxny : scale) * dc[i];
         }
         const double p0 = pos + wave_before(run, lane);
-        pos = __shfl(p0 + run, last, 64);
+        pos = __shfl(p0 + run, last(sg), 64);
 #pragma unroll
         for (int i = 0; i < Q; ++i) p[i] += p0;
     };
@@ -194,7 +196,7 @@ __device__ __forceinline__ void z_zero_column(R *S_, const double *zrow, double 
         sweep(sg);
         sx += wt[0] * p[0] + wt[1] * p[1] + wt[2] * p[2] + wt[3] * p[3];
     }
-    sx = wave_total(sx, lane, last);
+    sx = wave_total(sx, lane, last(0));
     const double mean = STR ? sx / hsum : sx / nz;
     sum = pos = 0.0;
     for (int sg = 0; sg < nseg; ++sg) {
@@ -680,11 +682,10 @@ __global__ __launch_bounds__(MAXT, sizeof(R) == 4 && L == 16 ? 4 : 1) void k_z_w
         }
     }
 
-    // scaled where phase 2 takes them (as in ZWBody); the zero mode has none
-    auto rhs = [&](int i, int v) -> R {
-        const R sc = R(STR ? zr(s + i, 2) * a.inv_nxny : scale);
-        return d[i][v] * (v == 0 && zero_lane ? R(0) : sc);
-    };
+    // uniform rows are scaled where phase 2 takes them (as in ZWBody),
+    // stretched ones with their coefficients in phase 1, whose wait for the
+    // row table covers the columns' loads; the zero mode's result is not stored
+    auto rhs = [&](int i, int v) -> R { return STR ? d[i][v] : d[i][v] * R(scale); };
 
     // ---- phase 1: Moebius product of the chunk (v recurrence) -----------
     R p00[V], p01[V], p10[V], p11[V];
@@ -699,6 +700,7 @@ __global__ __launch_bounds__(MAXT, sizeof(R) == 4 && L == 16 ? 4 : 1) void k_z_w
         for (int v = 0; v < V; ++v) {
             R x0, y0;
             if constexpr (STR) {
+                d[i][v] *= R(zr(k, 2) * a.inv_nxny);
                 const R ak = zt(k, 0), ck = zt(k, 1);
                 const R sd = sv[v] * zt(k, 2) + zt(k, 3);
                 const R inv = rcp_nr(sd + ck);
