@@ -291,7 +291,9 @@ int poisson_plan_autotune(poisson_plan plan, int flags);
 
 /*
  * Text description of the plan: one line per shape group with its grid,
- * boundary, precision, number of problems and chosen launch variants.
+ * boundary, precision, number of problems, chosen launch variants and whether
+ * a solve transforms whole z-planes along x and y in one launch (xy=plane) or
+ * in a pass each (xy=separate).
  * Writes at most len bytes (NUL-terminated) to buf; returns INVALID_ARG if
  * the text was truncated or an argument is null.
  */

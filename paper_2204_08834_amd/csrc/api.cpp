@@ -856,10 +856,7 @@ int pass_x_fwd(LSet &L, bool residual, bool want_partials, bool sum = true)
     int rc;
     const bool plane = !residual && !div && use_plane(L);
     const void *twy = g.tab.twy[L.prec == P_F32 ? 1 : 0]->p;
-    if (plane) {
-        np = g.d.nz;  // one record per plane
-        bytes = (double)g.N * (8.0 + sb) * L.n;
-    }
+    if (plane) np = g.d.nz;  // one record per plane
     if (L.p->rec) {
         Rec r;
         r.kind = residual ? RK_XR : (plane ? RK_PF : RK_XF);
@@ -2290,7 +2287,7 @@ int poisson_plan_describe(poisson_plan plan, char *buf, int len)
         const Group &g = plan->groups[gi];
         snprintf(line, sizeof line,
                  "group %zu: %dx%dx%d %s %s problems=%zu z_tile=%d y_tile=%d reverse=%d "
-                 "march_planes=%d check_planes=%d %s\n",
+                 "march_planes=%d check_planes=%d xy=%s %s\n",
                  gi,
                  g.d.nx, g.d.ny, g.d.nz,
                  g.d.bc_z == POISSON_BC_NEUMANN
@@ -2300,7 +2297,8 @@ int poisson_plan_describe(poisson_plan plan, char *buf, int len)
                                                  : (plan->precision == POISSON_FP32 ? "fp32"
                                                                                      : "fp32_refine"),
                  g.members.size(), g.tune.zv, g.tune.yv, g.tune.rev, std::abs(g.tune.kr),
-                 std::abs(g.tune.krc), g.tune.tuned ? "tuned" : "default");
+                 std::abs(g.tune.krc), g.plane ? "plane" : "separate",
+                 g.tune.tuned ? "tuned" : "default");
         out += line;
     }
     snprintf(buf, (size_t)len, "%s", out.c_str());

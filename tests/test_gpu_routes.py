@@ -1,0 +1,75 @@
+"""Which launches a plan takes: the plane passes (both transforms of a z-plane
+by one workgroup) or a pass each along x and y, the plane-range depths of the
+marches, and the tuner's y tile.  The fields of each route are compared with
+the FP64 oracle, as in the other parity tests."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2204_08834_amd import inputs  # noqa: E402
+
+PER, NEU, DIR = 0, 1, 2
+EPS = 2.0 ** -52
+
+
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_08834_amd import poisson
+    poisson.lib()
+    return poisson
+
+
+def _kappa(shape, sp, bc_z):
+    """Condition number of the operator periodic in x and y."""
+    lo, hi = [], 0.0
+    for n, h, per in ((shape[0], sp[0], True), (shape[1], sp[1], True), (shape[2], sp[2], bc_z == PER)):
+        if n == 1:
+            continue
+        m = np.arange(n) + (1 if not per and bc_z == DIR else 0)
+        lam = 4 / h ** 2 * np.sin(np.pi * m / (n if per else 2 * n)) ** 2
+        lo.append(lam[lam > 0].min())
+        hi += lam.max()
+    return hi / min(lo)
+
+
+def _check(orc, P, nx, ny, nz, bc, precision, route, **kw):
+    sp = (1.0 / nx, 1.0 / nx, 1.0 / nx)
+    f = inputs.uniform_velocity_rhs(nx, ny, nz, nx * sp[0], ny * sp[1], nz * sp[2], bc, 29)
+    rhs = torch.from_numpy(f).cuda()
+    print(f"[routes] {nx}x{ny}x{nz} bc {bc} {precision} {route}", flush=True)
+    with P.Plan(nx, ny, nz, *sp, bc, precision, bc_x=kw.get("bc_x", PER), bc_y=kw.get("bc_y", PER)) as plan:
+        assert f" xy={route} " in plan.describe()
+        out, st = plan.solve(rhs, torch.full_like(rhs, float("nan")))
+        torch.cuda.synchronize()
+    p = out.cpu().numpy()
+    if precision == "fp64":
+        ref = orc.solve(f, *sp, bc, **kw)
+        err = np.linalg.norm(p - ref) / np.linalg.norm(ref)
+        assert err <= max(1e-12, 4 * _kappa((nx, ny, nz), sp, bc) * EPS), err
+    else:
+        res, _ = orc.residual(f, p, *sp, bc, **kw)
+        assert st["status"] == 0 and res <= 1e-10, res
+
+
+# the largest planes of each precision with enough of them, the smallest, and
+# what has no plane pass: more values than fit, a length without a class, walls
+ROUTES = [
+    ("fp64", 24, 2, 3, "plane"), ("fp64", 128, 128, 16, "plane"), ("fp64", 256, 64, 16, "plane"),
+    ("fp64", 24, 512, 3, "plane"), ("fp32_refine", 192, 96, 8, "plane"),
+    ("fp32_refine", 256, 128, 64, "plane"), ("fp64", 256, 128, 4, "separate"),
+    ("fp64", 384, 8, 4, "separate"), ("fp32_refine", 256, 256, 3, "separate"),
+]
+
+
+@pytest.mark.parametrize("case", ROUTES, ids=["-".join(map(str, c)) for c in ROUTES])
+def test_transform_route(orc, case):
+    precision, nx, ny, nz, route = case
+    _check(orc, _gpu(), nx, ny, nz, NEU, precision, route)
+
+
+def test_walls_along_y_take_separate_passes(orc):
+    _check(orc, _gpu(), 64, 32, 6, NEU, "fp64", "separate", bc_y=NEU)
