@@ -417,7 +417,7 @@ struct Group {
     std::shared_ptr<DevBuf> S32;       // FP32 spectra, one per member
     std::shared_ptr<DevBuf> P32;       // refinement: FP32 first iterates, one per member
     std::shared_ptr<DevBuf> partials;  // per-workgroup partial sums, part_stride per member
-    bool plane = false;                // planes small enough for k_plane.hip (both transforms at once)
+    bool plane = false;                // k_plane.hip: both transforms of a plane at once
     int npart = 0;                     // workgroups of the forward x pass (upper bound)
     int part_stride = 0;               // doubles of partials per member
     Tune tune;                         // launch variants of this shape (autotuned)
@@ -691,9 +691,9 @@ int build_group(Group &g, Alloc &A)
     if ((rc = A.put(t.lamx, lx.data(), lx.size() * 8))) return rc;
     if ((rc = A.put(t.lamy, ly.data(), ly.size() * 8))) return rc;
     if ((rc = A.put(t.lamz, lz.data(), lz.size() * 8))) return rc;
-    g.plane = d.bc_x == POISSON_BC_PERIODIC && d.bc_y == POISSON_BC_PERIODIC &&
-              plane_fits(internal_prec(d.precision), d.nx, d.ny);
     const size_t n = g.members.size();
+    g.plane = d.bc_x == POISSON_BC_PERIODIC && d.bc_y == POISSON_BC_PERIODIC &&
+              plane_pays(internal_prec(d.precision), d.nx, d.ny, (long)d.nz * n);
     g.npart = x_fwd_blocks(internal_prec(d.precision), d.nx, d.ny, d.nz, 0, 0);
     g.part_stride = partial_slots(d) * 4;
     if ((rc = A.get(g.partials, (size_t)g.part_stride * sizeof(double) * n))) return rc;

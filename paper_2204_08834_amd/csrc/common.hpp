@@ -356,8 +356,9 @@ int launch_x_inv(int prec, const XInvArgs &a, hipStream_t s);
 int launch_y(int prec, const YArgs &a, hipStream_t s);
 // x and y together, one workgroup per plane (periodic x and y, plain input):
 // planes that fit a workgroup's LDS only.  The forward pass writes one
-// partial record per plane.
-bool plane_fits(int prec, int nx, int ny);
+// partial record per plane.  plane_pays: such a plane fits, and a launch over
+// `planes` of them takes no longer than the separate passes.
+bool plane_pays(int prec, int nx, int ny, long planes);
 int launch_plane_fwd(int prec, const PlaneFwd &a, hipStream_t s);
 int launch_plane_inv(int prec, const PlaneInv &a, hipStream_t s);
 int launch_plane_fwd_list(int prec, const PlaneFwd *a, int n, hipStream_t s);

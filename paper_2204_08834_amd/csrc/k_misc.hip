@@ -39,12 +39,12 @@ int launch_plane_fwd_list_f32(const PlaneFwd *, int, hipStream_t);
 int launch_plane_fwd_list_f64(const PlaneFwd *, int, hipStream_t);
 int launch_plane_inv_list_f32(const PlaneInv *, int, hipStream_t);
 int launch_plane_inv_list_f64(const PlaneInv *, int, hipStream_t);
-bool plane_fits_f32(int, int);
-bool plane_fits_f64(int, int);
+bool plane_pays_f32(int, int, long);
+bool plane_pays_f64(int, int, long);
 
-bool plane_fits(int prec, int nx, int ny)
+bool plane_pays(int prec, int nx, int ny, long planes)
 {
-    return prec == P_F32 ? plane_fits_f32(nx, ny) : plane_fits_f64(nx, ny);
+    return prec == P_F32 ? plane_pays_f32(nx, ny, planes) : plane_pays_f64(nx, ny, planes);
 }
 int launch_plane_fwd(int prec, const PlaneFwd &a, hipStream_t s)
 {

@@ -12,7 +12,8 @@
 // separate passes -> planes: 32^3 FP64 27.2 -> 21.2 us, 64^3 periodic 53.3 ->
 // 46.9, 128x128x64 FP64 64.8 -> 61.1, 96x96x48 FP32 + refinement 125.5 ->
 // 113.1, batch of 64 boxes FP32 + refinement 1016 -> 954, and 896 with the
-// tables fetched ahead of the field and the lists split by plane size.
+// tables fetched ahead of the field and the lists split by plane size.  Few
+// large planes keep the separate passes (plane_pays).
 //
 // The arithmetic is that of k_xpass.hip and k_ypass.hip (same radix plans,
 // tables and pair formulas).  The length along x is a compile-time constant,
@@ -678,11 +679,27 @@ static int run_planes(const A *a, int n, Cls cls_of, Launch launch, Own own)
 }  // namespace PK_NS
 using namespace PK_NS;
 
-bool PK_SUFFIX(plane_fits)(int nx, int ny)
+// A launch lasts as long as one workgroup takes for its plane, however few
+// planes there are, and for the largest planes that is longer than both
+// separate passes, which spread a plane over many workgroups.  Solves, us,
+// separate passes -> planes, by the planes in flight:
+//   FP32, 16 values per thread: 256x128 1 32 -> 41, 32 44 -> 48, 64 52 -> 54,
+//     96 70 -> 59; 192x96 1 1.07x, 48 1.00x, 64 0.96x; 64x384 48 1.09x, 96 0.95x
+//   FP64, more than 6144 values: 256x64 4 25 -> 28, 24 1.03x, 48 0.95x;
+//     128x128 12 29 -> 31, 48 0.98x
+//   FP64, 6144 values: 0.92x to 1.09x below 24 planes, 0.77x to 0.85x from 96;
+//   smaller planes: 0.63x to 1.00x at every count (FP32 to 0.92x).
+// 32x512 in FP64 (16 values a row) is level from one plane on and stays here
+// at every count: it is the one such shape whose two routes round differently,
+// and a problem's field must not depend on how many others its batch holds.
+bool PK_SUFFIX(plane_pays)(int nx, int ny, long planes)
 {
     int nt = 0;
     size_t lds = 0;
-    return plane_shape(nx, ny, nt, lds);
+    if (!plane_shape(nx, ny, nt, lds)) return false;
+    const int values = nx / 2 * ny;
+    if (sizeof(R) == 4) return planes >= (pl_ept(values) == 16 ? 64 : 1);
+    return planes >= (values > 6144 && nx != 32 ? 48 : 1);
 }
 
 #define PK_CASE_PF(N) \

@@ -58,10 +58,14 @@ def _check(orc, P, nx, ny, nz, bc, precision, route, **kw):
 # the largest planes of each precision with enough of them, the smallest, and
 # what has no plane pass: more values than fit, a length without a class, walls
 ROUTES = [
-    ("fp64", 24, 2, 3, "plane"), ("fp64", 128, 128, 16, "plane"), ("fp64", 256, 64, 16, "plane"),
-    ("fp64", 24, 512, 3, "plane"), ("fp32_refine", 192, 96, 8, "plane"),
-    ("fp32_refine", 256, 128, 64, "plane"), ("fp64", 256, 128, 4, "separate"),
-    ("fp64", 384, 8, 4, "separate"), ("fp32_refine", 256, 256, 3, "separate"),
+    ("fp64", 24, 2, 3, "plane"), ("fp64", 128, 128, 48, "plane"), ("fp64", 256, 64, 48, "plane"),
+    ("fp64", 24, 512, 3, "plane"), ("fp64", 32, 512, 2, "plane"), ("fp32_refine", 192, 96, 64, "plane"),
+    ("fp32_refine", 256, 128, 64, "plane"), ("fp32_refine", 128, 128, 2, "plane"),
+    ("fp64", 256, 128, 4, "separate"), ("fp64", 384, 8, 4, "separate"),
+    ("fp32_refine", 256, 256, 3, "separate"),
+    # few of the largest planes
+    ("fp64", 256, 64, 47, "separate"), ("fp64", 128, 128, 2, "separate"),
+    ("fp32_refine", 192, 96, 63, "separate"), ("fp32_refine", 256, 128, 2, "separate"),
 ]
 
 
@@ -73,3 +77,27 @@ def test_transform_route(orc, case):
 
 def test_walls_along_y_take_separate_passes(orc):
     _check(orc, _gpu(), 64, 32, 6, NEU, "fp64", "separate", bc_y=NEU)
+
+
+@pytest.mark.parametrize("shape", [(128, 128, 12), (256, 64, 12), (64, 256, 12), (32, 512, 12)])
+def test_route_by_planes_in_flight_keeps_fp64_fields(shape):
+    """A batch with enough planes takes the plane passes where one of its
+    problems alone takes the separate ones: the same FP64 field bitwise."""
+    P = _gpu()
+    nx, ny, nz = shape
+    spec = dict(nx=nx, ny=ny, nz=nz, dx=1.0 / nx, dy=1.0 / nx, dz=1.0 / nx, bc_z=NEU)
+    print(f"[routes] batch of 4 {nx}x{ny}x{nz}", flush=True)
+    rhs = [torch.from_numpy(inputs.random_rhs(nx, ny, nz, seed=60 + i)).cuda() for i in range(4)]
+    outs = [torch.full_like(r, float("nan")) for r in rhs]
+    bp = P.BatchPlan([spec] * 4, "fp64")
+    assert " xy=plane " in bp.describe()
+    bp.solve(rhs, outs)
+    torch.cuda.synchronize()
+    bp.close()
+    route = "plane" if nx == 32 else "separate"
+    with P.Plan(nx, ny, nz, 1.0 / nx, 1.0 / nx, 1.0 / nx, NEU, "fp64") as plan:
+        assert f" xy={route} " in plan.describe()
+        for r, o in zip(rhs, outs):
+            q, _ = plan.solve(r, torch.full_like(r, float("nan")))
+            torch.cuda.synchronize()
+            assert torch.equal(q, o)
