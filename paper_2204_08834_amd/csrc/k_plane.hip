@@ -26,6 +26,7 @@
 
 #include "fft_core.hpp"
 #include "lengths.hpp"
+#include "plane_lists.hpp"
 #include "stencil.hpp"
 
 #ifndef PK_REAL
@@ -627,21 +628,8 @@ static bool plane_shape(int nx, int ny, int &nt, size_t &lds)
 template <class A, class Cls, class Launch, class Own>
 static int run_planes(const A *a, int n, Cls cls_of, Launch launch, Own own)
 {
-    ListArgs<A> L{};
-    size_t lds = 0;
-    int total = 0, nt = 0;
-    auto flush = [&]() -> int {
-        if (L.nseg == 0) return 0;
-        // one shape alone: its own kernel, compiled for one length (FP32
-        // inverse: 72 VGPRs against the list's 109)
-        const bool single = L.nseg == 1;
-        L.start[L.nseg] = total;
-        if (!single) launch(L, total, nt, lds);
-        L.nseg = 0;
-        lds = 0;
-        total = nt = 0;
-        return single ? own(L.a[0]) : (int)hipGetLastError();
-    };
+    std::vector<PlaneSeg> segs;
+    std::vector<int> of, nts;  // record and threads of a segment
     for (int i = 0; i < n; ++i) {
         const auto &x = a[i].x;
         int t = 0;
@@ -652,28 +640,39 @@ static int run_planes(const A *a, int n, Cls cls_of, Launch launch, Own own)
             if (e) return e;
             continue;
         }
-        // a launch gives all its workgroups the LDS of its largest plane: much
-        // smaller planes get a launch of their own, with more of them per
-        // compute unit
-        if (L.nseg > 0 && 5 * b < 3 * lds) {
-            const int e = flush();
-            if (e) return e;
-        }
-        const int g = L.nseg++;
-        L.start[g] = total;
-        L.gx[g] = x.nz;
-        L.cls[g] = cls_of(x);
-        L.nt[g] = t;
-        L.a[g] = a[i];
-        total += x.nz * (x.batch ? x.nbatch : 1);
-        lds = lds > b ? lds : b;
-        nt = nt > t ? nt : t;
-        if (L.nseg == LIST_MAX_SEG) {
-            const int e = flush();
-            if (e) return e;
-        }
+        segs.push_back(PlaneSeg{b, (long)x.nz * (x.batch ? x.nbatch : 1)});
+        of.push_back(i);
+        nts.push_back(t);
     }
-    return flush();
+    for (const std::vector<int> &one : plane_launches(segs, LIST_MAX_SEG)) {
+        // one shape alone: its own kernel, compiled for one length (FP32
+        // inverse: 72 VGPRs against the list's 109)
+        int e = 0;
+        if (one.size() == 1) {
+            e = own(a[of[one[0]]]);
+        } else {
+            ListArgs<A> L{};
+            size_t lds = 0;
+            int total = 0, nt = 0;
+            for (int k : one) {
+                const A &r = a[of[k]];
+                const int g = L.nseg++;
+                L.start[g] = total;
+                L.gx[g] = r.x.nz;
+                L.cls[g] = cls_of(r.x);
+                L.nt[g] = nts[k];
+                L.a[g] = r;
+                total += (int)segs[k].planes;
+                lds = std::max(lds, segs[k].lds);
+                nt = std::max(nt, nts[k]);
+            }
+            L.start[L.nseg] = total;
+            launch(L, total, nt, lds);
+            e = (int)hipGetLastError();
+        }
+        if (e) return e;
+    }
+    return 0;
 }
 
 }  // namespace PK_NS

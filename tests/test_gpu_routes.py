@@ -101,3 +101,33 @@ def test_route_by_planes_in_flight_keeps_fp64_fields(shape):
             q, _ = plan.solve(r, torch.full_like(r, float("nan")))
             torch.cuda.synchronize()
             assert torch.equal(q, o)
+
+
+def test_plane_lists_of_deep_and_shallow_shapes(orc):
+    """Small deep planes and large shallow ones in one batch, enough of both
+    for a launch of their own, and shapes that share theirs: the oracle's
+    field, FP64 with every problem bitwise as its single plan solves it."""
+    P = _gpu()
+    shapes = [(64, 64, 96)] * 6 + [(128, 128, 16)] * 8 + [(48, 24, 30), (96, 32, 9)]
+    sp = [(1.0 / s[0],) * 3 for s in shapes]
+    fs = [inputs.random_rhs(*s, seed=80 + i) for i, s in enumerate(shapes)]
+    rhs = [torch.from_numpy(f).cuda() for f in fs]
+    specs = [dict(nx=s[0], ny=s[1], nz=s[2], dx=h[0], dy=h[1], dz=h[2], bc_z=NEU)
+             for s, h in zip(shapes, sp)]
+    for precision in ("fp64", "fp32_refine"):
+        print(f"[routes] deep and shallow planes {precision}", flush=True)
+        bp = P.BatchPlan(specs, precision)
+        assert "schedule=list" in bp.describe() and bp.describe().count("xy=plane") == 4
+        outs = [torch.full_like(r, float("nan")) for r in rhs]
+        bp.solve(rhs, outs)
+        torch.cuda.synchronize()
+        bp.close()
+        for i in (0, 6, 13, 14, 15):
+            if precision == "fp32_refine":
+                res, _ = orc.residual(fs[i], outs[i].cpu().numpy(), *sp[i], NEU)
+                assert res <= 1e-10, (i, res)
+                continue
+            with P.Plan(*shapes[i], *sp[i], NEU, precision) as plan:
+                q, _ = plan.solve(rhs[i], torch.full_like(rhs[i], float("nan")))
+                torch.cuda.synchronize()
+            assert torch.equal(q, outs[i]), i
