@@ -619,13 +619,17 @@ bool same_problem(const poisson_desc_t &a, const poisson_desc_t &b)
            a.dz == b.dz && a.bc_x == b.bc_x && a.bc_y == b.bc_y && a.bc_z == b.bc_z;
 }
 
-// z-planes per workgroup of the residual pass with transform (one problem, not
-// tuned): the depth whose workgroups fill the device's resident slots in the
+// z-planes per workgroup of the residual pass with transform (a plan of one
+// problem, not tuned): the depth whose workgroups fill the device's resident slots in the
 // fewest whole rounds with at most 24 planes each.  The plain depth of 8,
 // halved until there are 1024 workgroups, left the last round mostly empty or
 // took 4 planes where 11 fit: 256^3 69 -> 56 us, 512x256x64 40 -> 34,
 // 256x256x100 33 -> 29, 384x192x150 cavity 63 -> 58; 512x512x256, where 8
-// planes fill ten rounds, 219 and 218.
+// planes fill ten rounds, 219 and 218.  In a batch the shapes share a launch
+// (or overlap), so a depth that fills the device with one of them only re-reads
+// more planes: they keep the plain depth, halved by the problems of the launch
+// (one problem of each of eight shapes, 64^3 to 192x96x40, graph loop: 363 us
+// with exact depths, 348 without).
 int residual_depth(const poisson_desc_t &d, int plain)
 {
     const int slots = x_res_slots(d.nx, d.bc_x != POISSON_BC_PERIODIC ? 1 : 0, 1);
@@ -641,8 +645,8 @@ int residual_depth(const poisson_desc_t &d, int plain)
 }
 
 // Tables of the group in A (copied now, or staged in A's host image), then
-// the field-sized buffers
-int build_group(Group &g, Alloc &A)
+// the field-sized buffers; alone: the plan has this one problem
+int build_group(Group &g, Alloc &A, bool alone)
 {
     const poisson_desc_t &d = g.d;
     g.M = d.nx / 2;
@@ -703,7 +707,7 @@ int build_group(Group &g, Alloc &A)
     const bool refine = d.precision == POISSON_FP32_REFINE;
     if (refine && (rc = A.get(g.P32, (size_t)g.N * 4 * n))) return rc;
     g.tune = initial_tune(g.d, !g.hz.empty());
-    if (refine && n == 1 && !g.tune.tuned && !getenv("POISSON_MARCH_PLANES"))
+    if (refine && alone && !g.tune.tuned && !getenv("POISSON_MARCH_PLANES"))
         g.tune.kr = residual_depth(d, g.tune.kr);
     return POISSON_OK;
 }
@@ -1958,7 +1962,7 @@ int create_plan(const poisson_desc_t *descs, int count, void *stream, bool batch
     int off = 0;
     for (auto &g : p->groups) {
         Alloc A;
-        int rc = build_group(g, A);
+        int rc = build_group(g, A, count == 1);
         if (rc) return rc;
         g.host_off = off;
         off += (int)g.members.size();
@@ -2104,7 +2108,7 @@ int noalloc_build(NoAllocDevice &D, const poisson_desc_t &d, int dev, hipStream_
     A.base = D.base;
     A.cap = POISSON_NOALLOC_SCRATCH_BYTES;
     A.image = &D.image;
-    int rc = build_group(g, A);
+    int rc = build_group(g, A, true);
     if (!rc) rc = A.get(p->scalars, state_bytes(1));
     if (rc == POISSON_ERR_OUT_OF_MEMORY) {
         fprintf(stderr,

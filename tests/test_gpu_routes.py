@@ -131,3 +131,22 @@ def test_plane_lists_of_deep_and_shallow_shapes(orc):
                 q, _ = plan.solve(rhs[i], torch.full_like(rhs[i], float("nan")))
                 torch.cuda.synchronize()
             assert torch.equal(q, outs[i]), i
+
+
+def test_residual_depth_fits_one_problem_only(monkeypatch):
+    """An exact residual depth is chosen for a plan of one problem; the shapes
+    of a batch keep the plain depth, halved by the problems of the launch."""
+    P = _gpu()
+    for v in ("POISSON_MARCH_PLANES", "POISSON_AUTOTUNE", "POISSON_TUNE_CACHE"):
+        monkeypatch.delenv(v, raising=False)
+    specs = [dict(nx=n, ny=n, nz=nz, dx=1.0 / n, dy=1.0 / n, dz=1.0 / n, bc_z=NEU)
+             for n, nz in ((64, 66), (128, 62), (96, 50))]
+    bp = P.BatchPlan(specs, "fp32_refine")
+    assert bp.describe().count("march_planes=8 ") == 3, bp.describe()
+    bp.close()
+    for s in specs:
+        with P.Plan(**s, precision="fp32_refine") as plan:
+            assert "march_planes=8 " not in plan.describe(), plan.describe()
+        one = P.BatchPlan([s], "fp32_refine")  # a batch of one is one problem
+        assert "march_planes=8 " not in one.describe()
+        one.close()
