@@ -267,6 +267,7 @@ struct Tune {
     int zv = 0, yv = 0, rev = 1;
     int kr = 8;          // z-planes per workgroup of the residual pass with transform
     int krc = 8;         // the same for the residual check (negative: exact depth)
+    bool kr_own = false; // kr is residual_depth()'s: for the residual pass alone
     bool tuned = false;  // chosen by timing (else the defaults below)
 };
 
@@ -707,8 +708,10 @@ int build_group(Group &g, Alloc &A, bool alone)
     const bool refine = d.precision == POISSON_FP32_REFINE;
     if (refine && (rc = A.get(g.P32, (size_t)g.N * 4 * n))) return rc;
     g.tune = initial_tune(g.d, !g.hz.empty());
-    if (refine && alone && !g.tune.tuned && !getenv("POISSON_MARCH_PLANES"))
+    if (refine && alone && !g.tune.tuned && !getenv("POISSON_MARCH_PLANES")) {
         g.tune.kr = residual_depth(d, g.tune.kr);
+        g.tune.kr_own = true;
+    }
     return POISSON_OK;
 }
 
@@ -843,9 +846,9 @@ int pass_x_fwd(LSet &L, bool residual, bool want_partials, bool sum = true)
         // projection: f = alpha D(u, v, w) evaluated on the fly (one problem)
         const auto &pj = L.p->proj;
         a.residual = 2;
-        // an untuned exact depth is residual_depth()'s, chosen for the residual
-        // pass; this march keeps the plain depth
-        if (!g.tune.tuned && g.tune.kr < 0) a.kr_max = 0;
+        // residual_depth() chose for the residual pass; this march keeps the
+        // plain depth
+        if (g.tune.kr_own) a.kr_max = 0;
         a.u = pj.u;
         a.v = pj.v;
         a.w = pj.w;
@@ -1817,6 +1820,7 @@ int autotune_group(poisson_plan p, Group &g)
             return pass_x_fwd(L, true, true);
         });
         g.tune.kr = cr[idx];
+        g.tune.kr_own = false;
         idx = 1;
         pick(idx, nc, [&] {
             g.tune.krc = cc[idx];

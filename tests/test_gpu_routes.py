@@ -150,3 +150,25 @@ def test_residual_depth_fits_one_problem_only(monkeypatch):
         one = P.BatchPlan([s], "fp32_refine")  # a batch of one is one problem
         assert "march_planes=8 " not in one.describe()
         one.close()
+
+
+@pytest.mark.parametrize("planes", [4, 11])
+def test_exact_depth_from_the_environment_reaches_the_divergence(planes, monkeypatch):
+    """POISSON_MARCH_PLANES sets the depth of the projection's divergence march
+    too, exact depths included: its partial sums number one per y-row block and
+    range of planes (the sum pass reads 32 bytes of each).  4 planes are halved
+    for a small grid, to one."""
+    P = _gpu()
+    nx, ny, nz = 64, 64, 44
+    sums = {}
+    for k in (planes, nz):
+        monkeypatch.setenv("POISSON_MARCH_PLANES", str(k))
+        u, v, w = (torch.from_numpy(inputs.random_rhs(nx, ny, nz, seed=90 + i)).cuda() for i in range(3))
+        print(f"[routes] projection {nx}x{ny}x{nz} depth {k}", flush=True)
+        with P.Plan(nx, ny, nz, 1.0 / nx, 1.0 / nx, 1.0 / nx, NEU, "fp32") as plan:
+            plan.set_timing(True)
+            plan.project(u, v, w)
+            torch.cuda.synchronize()
+            sums[k] = plan.timing()["sum_partials"]["bytes_per_launch"] / 32
+    ranges = {4: nz, 11: 4}[planes]
+    assert sums[planes] == ranges * sums[nz], sums
