@@ -1725,7 +1725,8 @@ int solve_device(poisson_plan p, const double *const *rhs, double *const *sol,
 // shape (one problem, zero data: the passes are bandwidth-bound and take no
 // data-dependent paths) and keeps the fastest, one knob after the other: the
 // z-solve tile, the y tile and radix order, the block order.  Each candidate
-// is scored on the whole pass sequence (one warm-up, then the mean of three).
+// is scored on the whole pass sequence (one warm-up, then the mean of three);
+// the y tile of plane-sized shapes on the forward y pass and the z solve.
 int autotune_group(poisson_plan p, Group &g)
 {
     const int prec = internal_prec(p->precision);
@@ -1780,7 +1781,19 @@ int autotune_group(poisson_plan p, Group &g)
     // last-level cache
     auto whole = [&] { return solve_passes(L, false, false); };
     if (g.d.bc_z != POISSON_BC_PERIODIC) pick(g.tune.zv, 4, whole);
-    if (g.d.ny >= 64 && !g.plane) pick(g.tune.yv, g.d.bc_y == POISSON_BC_PERIODIC ? 4 : 2, whole);
+    // a solve of plane passes runs no y pass: the corrections and the projection
+    // run the forward one, and the z solve reads what it leaves in the cache
+    auto y_then_z = [&] {
+        const int e = pass_y(L, false);
+        return e ? e : pass_z(L);
+    };
+    if (g.d.ny >= 64) {
+        const int n = g.d.bc_y == POISSON_BC_PERIODIC ? 4 : 2;
+        if (g.plane)
+            pick(g.tune.yv, n, y_then_z);
+        else
+            pick(g.tune.yv, n, whole);
+    }
     pick(g.tune.rev, 2, whole);
     if (p->precision == POISSON_FP32_REFINE) {
         // plane-range depths of the residual pass with transform and of the

@@ -172,3 +172,25 @@ def test_exact_depth_from_the_environment_reaches_the_divergence(planes, monkeyp
             sums[k] = plan.timing()["sum_partials"]["bytes_per_launch"] / 32
     ranges = {4: nz, 11: 4}[planes]
     assert sums[planes] == ranges * sums[nz], sums
+
+
+def test_y_tile_is_tuned_where_planes_fit(tmp_path, monkeypatch):
+    """The corrections and the projection of a plane-sized problem run the
+    forward y pass: the tuner picks its tile by timing, whatever tile the plan
+    was created with (eight forced starts are not all recorded as chosen)."""
+    P = _gpu()
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("POISSON_TUNE_CACHE", str(cache))
+    nx, ny, nz = 64, 128, 64
+    forced, chosen = [], []
+    for v in (0, 1, 2, 3) * 2:
+        monkeypatch.setenv("POISSON_Y_VARIANT", str(v))
+        with P.Plan(nx, ny, nz, 1.0 / nx, 1.0 / nx, 1.0 / nx, NEU, "fp32_refine") as plan:
+            assert " xy=plane " in plan.describe()
+            plan.autotune(force=True)
+        line = next(ln for ln in cache.read_text().splitlines()
+                    if ln.startswith(f"f32 {nx} {ny} {nz} 001 "))
+        forced.append(v)
+        chosen.append(int(line.split(":")[1].split()[1]))
+    print("[routes] y tiles", chosen, flush=True)
+    assert all(0 <= c <= 3 for c in chosen) and chosen != forced
