@@ -209,6 +209,16 @@ __device__ __forceinline__ void z_zero_column(R *S_, const double *zrow, double 
     }
 }
 
+// Blocks ahead of the columns' tiles when there is a zero wavenumber: the first
+// solves it, the others leave at once.  Workgroups are dealt to the eight dies
+// in turn, and the passes before and after find in a die's L2 what the same
+// tile left there: with one leading block alone every tile moved on by a die
+// (512x128x32 walls in x and z, FP64, forward order, us: inverse y pass 10 ->
+// 16, solve 60 -> 74; 512x128x64 FP32, default order: 71 -> 76; the seven idle
+// blocks cost up to 0.2 us on the smallest boxes).
+constexpr int ZERO_BLOCKS = 8;
+static int zero_blocks(const ZArgs &a) { return a.regular ? 0 : ZERO_BLOCKS; }
+
 // L rows of a column from its chunk's first row, `rows` of them in the grid
 // (the rest zero).  All loads are issued before the first is used: in the
 // two-mode columns a row's value goes to the other lane half at once, and
@@ -250,7 +260,7 @@ template <int L, int W, bool STR = false> struct ZWBody {
             a.S = pq.S;
             if (a.zero_mean_out) a.zero_mean_out = pq.scal;
         }
-        // the first block takes the zero wavenumber
+        // the first block takes the zero wavenumber (ZERO_BLOCKS)
         int bx = vb.x, gx = vb.gx;
         if (!a.regular) {
             if (bx == 0) {
@@ -259,8 +269,9 @@ template <int L, int W, bool STR = false> struct ZWBody {
                                    a.inv_ntot, a.hsum);
                 return;
             }
-            bx -= 1;
-            gx -= 1;
+            if (bx < ZERO_BLOCKS) return;
+            bx -= ZERO_BLOCKS;
+            gx -= ZERO_BLOCKS;
         }
         // C*W slots of 4 reals in lane-contiguous groups (zw_slot)
         R *buf = (R *)smem_d;
@@ -615,7 +626,7 @@ __global__ __launch_bounds__(MAXT, sizeof(R) == 4 && L == 16 ? 4 : 1) void k_z_w
         if (a.zero_mean_out) a.zero_mean_out = pq.scal;
     }
     extern __shared__ double smem_d[];
-    // the first block takes the zero wavenumber
+    // the first block takes the zero wavenumber (ZERO_BLOCKS)
     int bx = blockIdx.x, gx = gridDim.x;
     if (!a.regular) {
         if (bx == 0) {
@@ -623,8 +634,9 @@ __global__ __launch_bounds__(MAXT, sizeof(R) == 4 && L == 16 ? 4 : 1) void k_z_w
                                a.dz2 * a.inv_nxny, a.inv_nxny, a.inv_ntot, a.hsum);
             return;
         }
-        bx -= 1;
-        gx -= 1;
+        if (bx < ZERO_BLOCKS) return;
+        bx -= ZERO_BLOCKS;
+        gx -= ZERO_BLOCKS;
     }
     // C*W slots of 4V reals, every field lane-contiguous (zw_slot)
     R *buf = (R *)smem_d;
@@ -883,7 +895,7 @@ static int run_zwr(const ZArgs &a, hipStream_t s)
     constexpr int MAXT = zwr_maxt<L>();
     const int C = (a.nz + L - 1) / L;
     if (C * W > MAXT || a.nx % ZR_V != 0) return -1;
-    const int nb = (a.ny * a.nx / ZR_V + W - 1) / W + (a.regular ? 0 : 1);
+    const int nb = (a.ny * a.nx / ZR_V + W - 1) / W + zero_blocks(a);
     const size_t shm = ((C * W * 4 * ZR_V * sizeof(R) + 7) / 8) * 8 +
                        (STR && sizeof(R) == 4 ? (size_t)C * L * 4 * sizeof(R) : 0);
     hipLaunchKernelGGL((k_z_walls_r<L, W, MAXT, STR>), dim3(nb, a.batch ? a.nbatch : 1),
@@ -902,7 +914,7 @@ static int run_zw(const ZArgs &a, hipStream_t s)
     const int nmain = a.xwall ? 0 : (a.ny * a.M + W - 1) / W;
     const size_t shm = ((C * W * 4 * sizeof(R) + 7) / 8) * 8 +
                        (STR && sizeof(R) == 4 ? (size_t)C * L * 4 * sizeof(R) : 0);
-    hipLaunchKernelGGL((k_z_walls<L, W, MAXT, STR>), dim3(nspecial + nmain + (a.regular ? 0 : 1), a.batch ? a.nbatch : 1),
+    hipLaunchKernelGGL((k_z_walls<L, W, MAXT, STR>), dim3(nspecial + nmain + zero_blocks(a), a.batch ? a.nbatch : 1),
                        dim3(W * C), shm, s, a, C, nspecial);
     return (int)hipGetLastError();
 }
@@ -969,7 +981,7 @@ static bool z_list_class(const ZArgs &a, int &cls, int &nt, int &gx, int &C, int
         const int H = W / 2 > 0 ? W / 2 : 1;
         nspecial = a.xwall ? npairs * ((a.M + H - 1) / H) : (npairs + H - 1) / H;
         const int nmain = a.xwall ? 0 : (a.ny * a.M + W - 1) / W;
-        gx = nspecial + nmain + (a.regular ? 0 : 1);
+        gx = nspecial + nmain + zero_blocks(a);
         lds = cls == 1 ? zw_lds_bytes<32>(C) : zw_lds_bytes<ZL_W2>(C);
         return true;
     }

@@ -194,3 +194,34 @@ def test_y_tile_is_tuned_where_planes_fit(tmp_path, monkeypatch):
         chosen.append(int(line.split(":")[1].split()[1]))
     print("[routes] y tiles", chosen, flush=True)
     assert all(0 <= c <= 3 for c in chosen) and chosen != forced
+
+
+def test_zero_mode_block_keeps_tiles_on_their_dies(monkeypatch):
+    """The workgroup of the zero wavenumber must not shift the z solve's tiles
+    to other dies than those whose L2 holds (and will be asked for) their
+    columns: the inverse y pass after a z solve with a zero mode takes what it
+    takes after one without (Dirichlet walls along x; the y pass is the same
+    kernel on the same sizes).  One leading block more, and not eight, made it
+    1.9 times as long at this size, where the spectrum fits the eight L2s."""
+    P = _gpu()
+    monkeypatch.setenv("POISSON_BLOCK_ORDER", "forward")
+    monkeypatch.setenv("POISSON_Y_VARIANT", "1")
+    nx, ny, nz = 512, 128, 32
+    f = torch.from_numpy(inputs.random_rhs(nx, ny, nz, seed=3)).cuda()
+    out = torch.empty_like(f)
+    best = {}
+    for bc_x in (NEU, DIR):
+        with P.Plan(nx, ny, nz, 1.0 / nx, 1.0 / nx, 1.0 / nx, NEU, "fp64", bc_x=bc_x) as plan:
+            plan.set_timing(True)
+            times = []
+            for _ in range(8):
+                plan.reset_timing()
+                for _ in range(10):
+                    plan.solve_async(f, out)
+                torch.cuda.synchronize()
+                t = plan.timing()["y_inv_f64"]
+                times.append(t["total_ms"] / t["launches"])
+            best[bc_x] = min(times)
+    print(f"[routes] y inverse after z, us: {1e3 * best[NEU]:.1f} with a zero mode, "
+          f"{1e3 * best[DIR]:.1f} without", flush=True)
+    assert best[NEU] <= 1.25 * best[DIR], best
