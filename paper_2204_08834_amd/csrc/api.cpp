@@ -715,6 +715,32 @@ int build_group(Group &g, Alloc &A, bool alone)
     return POISSON_OK;
 }
 
+// Batches where only some shapes take plane passes: their launch comes on top
+// of the other shapes' x and y launches, one after the other, instead of their
+// blocks filling those up.  That pays for 512 planes (two per compute unit) and
+// not for fewer (graph loops, us, planes -> all separate: 64x64x40 with
+// 256x256x40 FP32 + refinement 219 -> 198, FP64 120 -> 107; 8 shapes of 426
+// planes and 192x96x40 282 -> 252; 8 of 96x96x64 with 8 of 512x32x32, 512
+// planes, 337 against 358).  Planes of less than 2048 values are level either
+// way (three shapes up to 64x48 with 512x64x20: 236 -> 239) and stay; so does an FP64 batch in
+// which a shape's two routes round differently, so that an FP64 field does not
+// depend on the rest of its batch.
+void settle_planes(std::vector<Group> &groups)
+{
+    long planes = 0;
+    int values = 0;
+    bool separate = false, apart = false;
+    for (const Group &g : groups) {
+        separate = separate || !g.plane;
+        if (!g.plane) continue;
+        planes += (long)g.d.nz * (long)g.members.size();
+        values = std::max(values, g.M * g.d.ny);
+        apart = apart || (g.d.precision == POISSON_FP64 && plane_rounds_apart(g.d.nx, g.d.ny));
+    }
+    if (!separate || apart || planes >= 512 || values < 2048) return;
+    for (Group &g : groups) g.plane = false;
+}
+
 // ---------------------------------------------------------------------------
 // launch bookkeeping (optional per-pass hipEvent timing)
 // ---------------------------------------------------------------------------
@@ -1984,6 +2010,7 @@ int create_plan(const poisson_desc_t *descs, int count, void *stream, bool batch
         g.host_off = off;
         off += (int)g.members.size();
     }
+    settle_planes(p->groups);
     // scalars, then the control records, in one allocation (and one pinned copy)
     int rc = dev_alloc(p->scalars, state_bytes(count));
     if (rc) return rc;

@@ -359,6 +359,10 @@ int launch_y(int prec, const YArgs &a, hipStream_t s);
 // partial record per plane.  plane_pays: such a plane fits, and a launch over
 // `planes` of them takes no longer than the separate passes.
 bool plane_pays(int prec, int nx, int ny, long planes);
+// FP64 planes whose two routes differ in their roundings (all others give the
+// same bits): rows of 32, where the compiler contracts the split's products
+// differently, and 24x384, whose y passes have another radix order
+inline bool plane_rounds_apart(int nx, int ny) { return nx == 32 || (nx == 24 && ny == 384); }
 int launch_plane_fwd(int prec, const PlaneFwd &a, hipStream_t s);
 int launch_plane_inv(int prec, const PlaneInv &a, hipStream_t s);
 int launch_plane_fwd_list(int prec, const PlaneFwd *a, int n, hipStream_t s);

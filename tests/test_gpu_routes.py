@@ -225,3 +225,68 @@ def test_zero_mode_block_keeps_tiles_on_their_dies(monkeypatch):
     print(f"[routes] y inverse after z, us: {1e3 * best[NEU]:.1f} with a zero mode, "
           f"{1e3 * best[DIR]:.1f} without", flush=True)
     assert best[NEU] <= 1.25 * best[DIR], best
+
+
+def test_mixed_batches_of_few_planes_take_separate_passes(orc):
+    """Plane groups beside others, fewer than 512 planes: every shape takes the
+    separate passes, with the FP64 fields of the single plans bitwise.  512
+    planes, planes of few values, and FP64 rows of 32 keep the plane passes."""
+    P = _gpu()
+
+    def batch(shapes, precision):
+        return P.BatchPlan([dict(nx=s[0], ny=s[1], nz=s[2], dx=1.0 / s[0], dy=1.0 / s[0],
+                                 dz=1.0 / s[0], bc_z=NEU) for s in shapes], precision)
+
+    other = (256, 256, 4)
+    for shapes, precision, planes in (
+            ([(64, 64, 40), other], "fp64", 0), ([(64, 64, 40), other], "fp32_refine", 0),
+            ([(64, 64, 128)] * 4 + [other], "fp64", 1), ([(64, 64, 127)] * 4 + [other], "fp64", 0),
+            ([(64, 48, 9), (24, 24, 5), other], "fp64", 2), ([(64, 64, 9), (48, 24, 9)], "fp64", 2),
+            ([(64, 64, 9), (32, 16, 4), other], "fp64", 2),
+            ([(64, 64, 9), (32, 16, 4), other], "fp32", 0)):
+        bp = batch(shapes, precision)
+        assert bp.describe().count(" xy=plane ") == planes, (shapes, precision, bp.describe())
+        bp.close()
+    for precision in ("fp64", "fp32_refine"):
+        shapes = [(64, 64, 40), (128, 96, 7), other]
+        print(f"[routes] mixed batch {precision}", flush=True)
+        fs = [inputs.random_rhs(*s, seed=70 + i) for i, s in enumerate(shapes)]
+        rhs = [torch.from_numpy(f).cuda() for f in fs]
+        outs = [torch.full_like(r, float("nan")) for r in rhs]
+        bp = batch(shapes, precision)
+        bp.solve(rhs, outs)
+        torch.cuda.synchronize()
+        bp.close()
+        for s, f, r, o in zip(shapes, fs, rhs, outs):
+            h = (1.0 / s[0],) * 3
+            if precision == "fp32_refine":
+                res, _ = orc.residual(f, o.cpu().numpy(), *h, NEU)
+                assert res <= 1e-10, (s, res)
+                continue
+            with P.Plan(*s, *h, NEU, precision) as plan:
+                q, _ = plan.solve(r, torch.full_like(r, float("nan")))
+                torch.cuda.synchronize()
+            assert torch.equal(q, o), s
+
+
+@pytest.mark.parametrize("nx", [24, 32, 48, 64, 96, 128, 192, 256])
+def test_fp64_routes_give_the_same_bits(nx):
+    """Plane passes against separate ones (which per-pass timing runs), every
+    plane size of FP64: the same bits but for rows of 32 and for 24x384, whose
+    routes the plan never mixes."""
+    P = _gpu()
+    for ny in (2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512):
+        if nx // 2 * ny > 8192:
+            continue
+        nz = 48 if nx // 2 * ny > 6144 else 3
+        f = torch.from_numpy(inputs.random_rhs(nx, ny, nz, seed=ny)).cuda()
+        with P.Plan(nx, ny, nz, 1.0 / nx, 1.0 / ny, 1.0 / nz, NEU, "fp64") as plan:
+            assert " xy=plane " in plan.describe()
+            a, _ = plan.solve(f, torch.full_like(f, float("nan")))
+            plan.set_timing(True)
+            b, _ = plan.solve(f, torch.full_like(f, float("nan")))
+            torch.cuda.synchronize()
+        if nx == 32 or (nx, ny) == (24, 384):
+            assert torch.allclose(a, b, rtol=0, atol=1e-12 * float(b.abs().max())), (nx, ny)
+        else:
+            assert torch.equal(a, b), (nx, ny)
