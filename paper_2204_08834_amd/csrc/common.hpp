@@ -276,6 +276,7 @@ struct ZArgs {
     int gate;
     int dirichlet_z;        // walls with zero value (ghost = -wall cell) instead of zero gradient
     int regular;            // no null space (a Dirichlet wall on some axis): no zero mode
+    int lead;               // walls: blocks ahead of the tiles (set by the launcher)
     int ywall;              // walls along y: the m = 0 column holds A + iB with real y-modes
     int xwall;              // walls along x: every column m holds the real x-modes 2m, 2m+1
     int periodic_z;         // 1: periodic z (transform), 0: walls (tridiagonal solve)

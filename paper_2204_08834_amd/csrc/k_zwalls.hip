@@ -214,10 +214,16 @@ __device__ __forceinline__ void z_zero_column(R *S_, const double *zrow, double 
 // in turn, and the passes before and after find in a die's L2 what the same
 // tile left there: with one leading block alone every tile moved on by a die
 // (512x128x32 walls in x and z, FP64, forward order, us: inverse y pass 10 ->
-// 16, solve 60 -> 74; 512x128x64 FP32, default order: 71 -> 76; the seven idle
-// blocks cost up to 0.2 us on the smallest boxes).
-constexpr int ZERO_BLOCKS = 8;
-static int zero_blocks(const ZArgs &a) { return a.regular ? 0 : ZERO_BLOCKS; }
+// 16, solve 60 -> 74; 512x128x64 FP32, default order: 71 -> 76; 16 of 64^3 with
+// walls in x and z, FP32 + refinement 222 -> 217; the seven idle blocks cost up
+// to 0.2 us on the smallest boxes).  Several problems of few tiles each take one
+// block: seven idle ones beside 18 tiles cost 64 problems of 32x32x64 134 against
+// 129 us (FP64, graph loop).
+static int lead_blocks(const ZArgs &a, int tiles)
+{
+    if (a.regular) return 0;
+    return a.batch && a.nbatch > 1 && tiles < 64 ? 1 : 8;
+}
 
 // L rows of a column from its chunk's first row, `rows` of them in the grid
 // (the rest zero).  All loads are issued before the first is used: in the
@@ -260,7 +266,7 @@ template <int L, int W, bool STR = false> struct ZWBody {
             a.S = pq.S;
             if (a.zero_mean_out) a.zero_mean_out = pq.scal;
         }
-        // the first block takes the zero wavenumber (ZERO_BLOCKS)
+        // the first block takes the zero wavenumber (lead_blocks)
         int bx = vb.x, gx = vb.gx;
         if (!a.regular) {
             if (bx == 0) {
@@ -269,9 +275,9 @@ template <int L, int W, bool STR = false> struct ZWBody {
                                    a.inv_ntot, a.hsum);
                 return;
             }
-            if (bx < ZERO_BLOCKS) return;
-            bx -= ZERO_BLOCKS;
-            gx -= ZERO_BLOCKS;
+            if (bx < a.lead) return;
+            bx -= a.lead;
+            gx -= a.lead;
         }
         // C*W slots of 4 reals in lane-contiguous groups (zw_slot)
         R *buf = (R *)smem_d;
@@ -626,7 +632,7 @@ __global__ __launch_bounds__(MAXT, sizeof(R) == 4 && L == 16 ? 4 : 1) void k_z_w
         if (a.zero_mean_out) a.zero_mean_out = pq.scal;
     }
     extern __shared__ double smem_d[];
-    // the first block takes the zero wavenumber (ZERO_BLOCKS)
+    // the first block takes the zero wavenumber (lead_blocks)
     int bx = blockIdx.x, gx = gridDim.x;
     if (!a.regular) {
         if (bx == 0) {
@@ -634,9 +640,9 @@ __global__ __launch_bounds__(MAXT, sizeof(R) == 4 && L == 16 ? 4 : 1) void k_z_w
                                a.dz2 * a.inv_nxny, a.inv_nxny, a.inv_ntot, a.hsum);
             return;
         }
-        if (bx < ZERO_BLOCKS) return;
-        bx -= ZERO_BLOCKS;
-        gx -= ZERO_BLOCKS;
+        if (bx < a.lead) return;
+        bx -= a.lead;
+        gx -= a.lead;
     }
     // C*W slots of 4V reals, every field lane-contiguous (zw_slot)
     R *buf = (R *)smem_d;
@@ -890,12 +896,15 @@ __global__ __launch_bounds__(MAXT, sizeof(R) == 4 && L == 16 ? 4 : 1) void k_z_w
 template <int L> constexpr int zwr_maxt() { return (L == 16 ? 512 : 1024) / (sizeof(R) == 8 ? 2 : 1); }
 
 template <int L, int W, bool STR>
-static int run_zwr(const ZArgs &a, hipStream_t s)
+static int run_zwr(const ZArgs &a0, hipStream_t s)
 {
     constexpr int MAXT = zwr_maxt<L>();
+    ZArgs a = a0;
     const int C = (a.nz + L - 1) / L;
     if (C * W > MAXT || a.nx % ZR_V != 0) return -1;
-    const int nb = (a.ny * a.nx / ZR_V + W - 1) / W + zero_blocks(a);
+    const int tiles = (a.ny * a.nx / ZR_V + W - 1) / W;
+    a.lead = lead_blocks(a, tiles);
+    const int nb = tiles + a.lead;
     const size_t shm = ((C * W * 4 * ZR_V * sizeof(R) + 7) / 8) * 8 +
                        (STR && sizeof(R) == 4 ? (size_t)C * L * 4 * sizeof(R) : 0);
     hipLaunchKernelGGL((k_z_walls_r<L, W, MAXT, STR>), dim3(nb, a.batch ? a.nbatch : 1),
@@ -904,17 +913,19 @@ static int run_zwr(const ZArgs &a, hipStream_t s)
 }
 
 template <int L, int W, int MAXT, bool STR>
-static int run_zw(const ZArgs &a, hipStream_t s)
+static int run_zw(const ZArgs &a0, hipStream_t s)
 {
+    ZArgs a = a0;
     const int C = (a.nz + L - 1) / L;
     if (C * W > MAXT) return -1;
     const int npairs = a.ywall ? a.ny : a.ny / 2 + 1;
     constexpr int H = W / 2 > 0 ? W / 2 : 1;
     const int nspecial = a.xwall ? npairs * ((a.M + H - 1) / H) : (npairs + H - 1) / H;
     const int nmain = a.xwall ? 0 : (a.ny * a.M + W - 1) / W;
+    a.lead = lead_blocks(a, nspecial + nmain);
     const size_t shm = ((C * W * 4 * sizeof(R) + 7) / 8) * 8 +
                        (STR && sizeof(R) == 4 ? (size_t)C * L * 4 * sizeof(R) : 0);
-    hipLaunchKernelGGL((k_z_walls<L, W, MAXT, STR>), dim3(nspecial + nmain + zero_blocks(a), a.batch ? a.nbatch : 1),
+    hipLaunchKernelGGL((k_z_walls<L, W, MAXT, STR>), dim3(nspecial + nmain + a.lead, a.batch ? a.nbatch : 1),
                        dim3(W * C), shm, s, a, C, nspecial);
     return (int)hipGetLastError();
 }
@@ -959,10 +970,10 @@ __global__ __launch_bounds__(ZL_NT) void k_z_list(ListArgs<ZArgs>)
     }
 }
 
-// class, threads, blocks per problem, chunks, special blocks and LDS of a z
-// record in the list kernel; false when it has no class there
+// class, threads, blocks per problem, chunks, special and leading blocks and LDS
+// of a z record in the list kernel; false when it has no class there
 static bool z_list_class(const ZArgs &a, int &cls, int &nt, int &gx, int &C, int &nspecial,
-                         size_t &lds)
+                         int &lead, size_t &lds)
 {
     if (!a.periodic_z) {
         if ((a.xwall && a.ywall) || a.zrow) return false;
@@ -981,7 +992,8 @@ static bool z_list_class(const ZArgs &a, int &cls, int &nt, int &gx, int &C, int
         const int H = W / 2 > 0 ? W / 2 : 1;
         nspecial = a.xwall ? npairs * ((a.M + H - 1) / H) : (npairs + H - 1) / H;
         const int nmain = a.xwall ? 0 : (a.ny * a.M + W - 1) / W;
-        gx = nspecial + nmain + zero_blocks(a);
+        lead = lead_blocks(a, nspecial + nmain);
+        gx = nspecial + nmain + lead;
         lds = cls == 1 ? zw_lds_bytes<32>(C) : zw_lds_bytes<ZL_W2>(C);
         return true;
     }
@@ -1038,9 +1050,9 @@ int PK_SUFFIX(launch_z_list)(const ZArgs *a, int n, hipStream_t s)
         return (int)hipGetLastError();
     };
     for (int i = 0; i < n; ++i) {
-        int cls = 0, nt = 0, gx = 0, C = 0, nsp = 0;
+        int cls = 0, nt = 0, gx = 0, C = 0, nsp = 0, lead = 0;
         size_t b = 0;
-        if (!z_list_class(a[i], cls, nt, gx, C, nsp, b)) {
+        if (!z_list_class(a[i], cls, nt, gx, C, nsp, lead, b)) {
             const int e = a[i].periodic_z ? PK_SUFFIX(launch_z_periodic)(a[i], s)
                                           : PK_SUFFIX(launch_z_walls)(a[i], s);
             if (e) return e;
@@ -1054,6 +1066,7 @@ int PK_SUFFIX(launch_z_list)(const ZArgs *a, int n, hipStream_t s)
         L.aux[g] = C;
         L.aux2[g] = nsp;
         L.a[g] = a[i];
+        L.a[g].lead = lead;
         shorts = shorts && a[i].nz <= 64;
         total += gx * (a[i].batch ? a[i].nbatch : 1);
         lds = lds > b ? lds : b;
