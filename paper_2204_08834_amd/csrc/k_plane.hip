@@ -629,7 +629,7 @@ template <class A, class Cls, class Launch, class Own>
 static int run_planes(const A *a, int n, Cls cls_of, Launch launch, Own own)
 {
     std::vector<PlaneSeg> segs;
-    std::vector<int> of, nts;  // record and threads of a segment
+    std::vector<int> of;  // record of a segment
     for (int i = 0; i < n; ++i) {
         const auto &x = a[i].x;
         int t = 0;
@@ -640,9 +640,8 @@ static int run_planes(const A *a, int n, Cls cls_of, Launch launch, Own own)
             if (e) return e;
             continue;
         }
-        segs.push_back(PlaneSeg{b, (long)x.nz * (x.batch ? x.nbatch : 1)});
+        segs.push_back(PlaneSeg{b, t, (long)x.nz * (x.batch ? x.nbatch : 1)});
         of.push_back(i);
-        nts.push_back(t);
     }
     for (const std::vector<int> &one : plane_launches(segs, LIST_MAX_SEG)) {
         // one shape alone: its own kernel, compiled for one length (FP32
@@ -660,11 +659,11 @@ static int run_planes(const A *a, int n, Cls cls_of, Launch launch, Own own)
                 L.start[g] = total;
                 L.gx[g] = r.x.nz;
                 L.cls[g] = cls_of(r.x);
-                L.nt[g] = nts[k];
+                L.nt[g] = segs[k].threads;
                 L.a[g] = r;
                 total += (int)segs[k].planes;
                 lds = std::max(lds, segs[k].lds);
-                nt = std::max(nt, nts[k]);
+                nt = std::max(nt, segs[k].threads);
             }
             L.start[L.nseg] = total;
             launch(L, total, nt, lds);

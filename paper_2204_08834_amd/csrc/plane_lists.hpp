@@ -3,52 +3,78 @@
 #pragma once
 #include <algorithm>
 #include <cstddef>
-#include <numeric>
 #include <vector>
 
 namespace pk {
 
-// planes of one shape: LDS of a plane, planes (workgroups) of all problems
+// planes of one shape: LDS and threads of a plane, planes (workgroups) of all
+// problems
 struct PlaneSeg {
     size_t lds;
+    int threads;
     long planes;
 };
 
-// The launches, each a list of indices into `segs`.  Every workgroup of a
-// launch gets the LDS of its largest plane, so much smaller planes have a
-// launch of their own, with more of them per compute unit.  The launches run
-// one after the other, so a split pays only where the larger planes occupy
-// half of the 256 compute units and the smaller ones all of them twice.
-// Graph loops, us, always split -> one launch -> this rule:
-//   one problem of each of 7 shapes, FP64: 154 -> 102 -> 100
-//   16 of 64x64x96 and 8 of 128x128x16, FP64 169 -> 176 -> 165, FP32 + refinement
-//     314 -> 338 -> 309
-//   24 of 64^3, 24 of 96x96x48, 16 of 128x128x64, FP32 + refinement 910 -> 987 -> 908
-// Sorted by LDS, so that the rule sees every pair whichever shape comes first
-// (in the batch's order, by points, 64x64x96 comes before 128x128x16: its planes
-// were given four times the LDS they need, 188 and 353 us).
+// workgroups of this LDS and thread count that one compute unit holds
+inline int planes_per_cu(size_t lds, int threads)
+{
+    const long by_lds = (long)(160 * 1024 / lds), by_waves = 2048 / threads;
+    return (int)std::max(1L, std::min(by_lds, by_waves));
+}
+
+// The launches, each a list of indices into `segs` in their order (the largest
+// problems first, whose workgroups are dealt out first: 10 of 64x128x95 ahead of 6
+// of 96x96x35, FP64 forward, 42 us, behind them 47).  Every workgroup of a launch
+// gets the LDS of its largest plane, so much smaller planes gain from a launch of
+// their own, with more of them per compute unit; but launches run one after the
+// other, and each costs about the time of one plane.
 inline std::vector<std::vector<int>> plane_launches(const std::vector<PlaneSeg> &segs, int max_seg)
 {
-    constexpr long HELD = 128, REST = 512;
-    std::vector<int> order(segs.size());
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int b) { return segs[a].lds > segs[b].lds; });
+    std::vector<std::vector<int>> out;
     long rest = 0, held = 0;
     for (const PlaneSeg &s : segs) rest += s.planes;
-    std::vector<std::vector<int>> out;
-    for (int i : order) {
+    size_t most = 0, least = 0;  // LDS of the last launch's planes
+    const int n = (int)segs.size();
+    for (int i = 0; i < n; ++i) {
         const PlaneSeg &s = segs[i];
-        const bool full = !out.empty() && (int)out.back().size() == max_seg;
-        const bool small = !out.empty() && 5 * s.lds < 3 * segs[out.back()[0]].lds &&
-                           held >= HELD && rest >= REST;
-        if (out.empty() || full || small) {
+        // workgroup slots that planes [from, to) lose to an allotment of `lds`
+        auto lost = [&](int from, int to, size_t own, size_t lds) {
+            double slots = 0.0;
+            for (int k = from; k < to; ++k)
+                slots += (double)segs[k].planes * (1.0 / planes_per_cu(lds, segs[k].threads) -
+                                                   1.0 / planes_per_cu(own, segs[k].threads));
+            return slots;
+        };
+        bool cut = out.empty() || (int)out.back().size() == max_seg;
+        if (!cut && 5 * s.lds < 3 * most) {
+            // much smaller planes from here on: both sides have to fill the
+            // device, the smaller planes twice -- or nearly once where each
+            // side is one shape and gets the kernel of that shape.  Graph
+            // loops, us, always split -> one launch -> this rule:
+            //   one problem of each of 7 shapes, FP64: 150 -> 102 -> 101
+            //   24 of 64^3, 24 of 96x96x48, 16 of 128x128x64, FP32 + refinement:
+            //     922 -> 981 -> 922
+            //   11 of 96x128x84, 10 of 48x128x34, the same: 420 -> 438 -> 420
+            // The larger planes may be fewer where the others lose 300 slots.
+            cut = (held >= 256 && rest >= (n == 2 ? 320 : 512)) ||
+                  lost(i, n, s.lds, most) >= 300.0;
+        } else if (!cut && 5 * least < 3 * s.lds) {
+            // much larger planes (of fewer points).  16 of 64x64x96, 8 of
+            // 128x128x16: FP64 one launch 190 us, two 165; FP32 + refinement 352
+            // and 310
+            cut = lost(out.back()[0], i, most, s.lds) >= 300.0;
+        }
+        if (cut) {
             out.emplace_back();
             held = 0;
+            most = 0;
+            least = s.lds;
         }
         out.back().push_back(i);
         held += s.planes;
         rest -= s.planes;
+        most = std::max(most, s.lds);
+        least = std::min(least, s.lds);
     }
     return out;
 }
