@@ -717,27 +717,36 @@ int build_group(Group &g, Alloc &A, bool alone)
 
 // Batches where only some shapes take plane passes: their launch comes on top
 // of the other shapes' x and y launches, one after the other, instead of their
-// blocks filling those up.  That pays for 512 planes (two per compute unit) and
-// not for fewer (graph loops, us, planes -> all separate: 64x64x40 with
-// 256x256x40 FP32 + refinement 219 -> 198, FP64 120 -> 107; 8 shapes of 426
-// planes and 192x96x40 282 -> 252; 8 of 96x96x64 with 8 of 512x32x32, 512
-// planes, 337 against 358).  Planes of less than 2048 values are level either
-// way (three shapes up to 64x48 with 512x64x20: 236 -> 239) and stay; so does an FP64 batch in
-// which a shape's two routes round differently, so that an FP64 field does not
-// depend on the rest of its batch.
+// blocks filling those up.  That pays for 512 planes (two per compute unit) that
+// hold a third of the batch's points, and not for less.  Graph loops, us, planes
+// -> all separate:
+//   64x64x40 with 256x256x40: FP32 + refinement 219 -> 198, FP64 120 -> 107
+//   8 shapes of 426 planes and 192x96x40, FP32 + refinement: 282 -> 252
+//   690 planes of 64x128 and 48x64 with 9 of 192x96x54 (28 % of the points),
+//     FP64: 267 -> 254
+//   1062 planes of 128x64 and 192x32 with 8 of 192x128x60 (40 %), FP64: 344 -> 363
+//   8 of 96x96x64 with 8 of 512x32x32 (512 planes, 53 %), the refinement: 337 -> 358
+// Few planes of less than 2048 values are level either way and stay; so does an
+// FP64 batch in which a shape's two routes round differently, so that an FP64
+// field does not depend on the rest of its batch.
 void settle_planes(std::vector<Group> &groups)
 {
     long planes = 0;
     int values = 0;
+    double all = 0.0, held = 0.0;  // points, points of the plane shapes
     bool separate = false, apart = false;
     for (const Group &g : groups) {
+        const double n = (double)g.members.size();
+        all += n * (double)g.N;
         separate = separate || !g.plane;
         if (!g.plane) continue;
+        held += n * (double)g.N;
         planes += (long)g.d.nz * (long)g.members.size();
         values = std::max(values, g.M * g.d.ny);
         apart = apart || (g.d.precision == POISSON_FP64 && plane_rounds_apart(g.d.nx, g.d.ny));
     }
-    if (!separate || apart || planes >= 512 || values < 2048) return;
+    if (!separate || apart) return;
+    if (3.0 * held >= all && (planes >= 512 || values < 2048)) return;
     for (Group &g : groups) g.plane = false;
 }
 

@@ -228,9 +228,10 @@ def test_zero_mode_block_keeps_tiles_on_their_dies(monkeypatch):
 
 
 def test_mixed_batches_of_few_planes_take_separate_passes(orc):
-    """Plane groups beside others, fewer than 512 planes: every shape takes the
-    separate passes, with the FP64 fields of the single plans bitwise.  512
-    planes, planes of few values, and FP64 rows of 32 keep the plane passes."""
+    """Plane groups beside others, fewer than 512 planes or less than a third of
+    the points: every shape takes the separate passes, with the FP64 fields of the
+    single plans bitwise.  512 planes of a third of the points, few planes of few
+    values, and FP64 rows of 32 keep the plane passes."""
     P = _gpu()
 
     def batch(shapes, precision):
@@ -241,7 +242,10 @@ def test_mixed_batches_of_few_planes_take_separate_passes(orc):
     for shapes, precision, planes in (
             ([(64, 64, 40), other], "fp64", 0), ([(64, 64, 40), other], "fp32_refine", 0),
             ([(64, 64, 128)] * 4 + [other], "fp64", 1), ([(64, 64, 127)] * 4 + [other], "fp64", 0),
-            ([(64, 48, 9), (24, 24, 5), other], "fp64", 2), ([(64, 64, 9), (48, 24, 9)], "fp64", 2),
+            ([(64, 64, 128)] * 4 + [(256, 256, 70)], "fp64", 0),
+            ([(64, 48, 9), (24, 24, 5), (256, 256, 1)], "fp64", 0),
+            ([(64, 48, 14), (24, 24, 5), (256, 256, 1)], "fp64", 2),
+            ([(64, 64, 9), (48, 24, 9)], "fp64", 2),
             ([(64, 64, 9), (32, 16, 4), other], "fp64", 2),
             ([(64, 64, 9), (32, 16, 4), other], "fp32", 0)):
         bp = batch(shapes, precision)
