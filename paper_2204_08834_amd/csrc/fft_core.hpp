@@ -90,7 +90,8 @@ constexpr RPlan make_rplan(int n)
 // plan variant: 0 = the order above, 1 = the same radices in reverse order
 // (small radix first)
 // 2, 3 = three passes with a radix of 12 or 16 for lengths that take four
-// passes otherwise (the y transforms, YCfg)
+// passes otherwise (the y transforms, YCfg).  1536 (8, 8, 8, 3) has none here:
+// no three-pass order of it has been measured
 constexpr RPlan get_rplan(int n, int variant)
 {
     if (variant >= 2) {

@@ -565,9 +565,9 @@ int launch_widen(const float *src, double *dst, size_t n, hipStream_t s)
     return (int)hipGetLastError();
 }
 
-// zero n 4-byte words (control records and scalars of a plan whose state
-// must start cleared; a kernel rather than a memset so the clear also
-// behaves inside a captured graph)
+// zero n 4-byte words (the scratch fields that the schedule tuner times a batch
+// on; a kernel rather than a memset, whose node in a captured graph has given
+// wrong results on replays)
 __global__ __launch_bounds__(256) void k_zero_words(unsigned *dst, size_t n)
 {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
