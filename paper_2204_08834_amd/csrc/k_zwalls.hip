@@ -141,8 +141,8 @@ __device__ __forceinline__ double wave_total(double v, int lane, int last)
 // against 8.8 for the same 32^3 grid without a zero mode (FP64).
 // Beyond 256 rows the wavefront goes over the column in rounds of 256, three
 // times; the form before spread it over the chunks of its workgroup.  Whole
-// solves in FP64, before -> now, us: 64x64x512 85 -> 48, 32x32x1024 71 -> 42,
-// 32x32x4096 276 -> 239, 8x8x4096 174 -> 126.
+// solves, before -> now, us: 8x8x4096 FP64 174 -> 126, FP32 76 -> 65; 16x16x300
+// FP64 40 -> 29.
 template <bool STR>
 __device__ __forceinline__ void z_zero_column(R *S_, const double *zrow, double *mean_out, int nz,
                                            size_t stride, double scale, double inv_nxny,
