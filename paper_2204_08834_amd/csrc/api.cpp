@@ -698,7 +698,7 @@ int build_group(Group &g, Alloc &A, bool alone)
     if ((rc = A.put(t.lamz, lz.data(), lz.size() * 8))) return rc;
     const size_t n = g.members.size();
     g.plane = d.bc_x == POISSON_BC_PERIODIC && d.bc_y == POISSON_BC_PERIODIC &&
-              plane_pays(internal_prec(d.precision), d.nx, d.ny, (long)d.nz * n);
+              plane_pays(internal_prec(d.precision), d.nx, d.ny, d.nz, (long)n);
     g.npart = x_fwd_blocks(internal_prec(d.precision), d.nx, d.ny, d.nz, 0, 0);
     g.part_stride = partial_slots(d) * 4;
     if ((rc = A.get(g.partials, (size_t)g.part_stride * sizeof(double) * n))) return rc;
@@ -720,15 +720,15 @@ int build_group(Group &g, Alloc &A, bool alone)
 // blocks filling those up.  That pays for 512 planes (two per compute unit) that
 // hold a third of the batch's points, and not for less.  Graph loops, us, planes
 // -> all separate:
-//   64x64x40 with 256x256x40: FP32 + refinement 219 -> 198, FP64 120 -> 107
-//   8 shapes of 426 planes and 192x96x40, FP32 + refinement: 282 -> 252
+//   64x64x40 with 256x256x40, FP64: 120 -> 107
 //   690 planes of 64x128 and 48x64 with 9 of 192x96x54 (28 % of the points),
 //     FP64: 267 -> 254
 //   1062 planes of 128x64 and 192x32 with 8 of 192x128x60 (40 %), FP64: 344 -> 363
-//   8 of 96x96x64 with 8 of 512x32x32 (512 planes, 53 %), the refinement: 337 -> 358
-// Few planes of less than 2048 values are level either way and stay; so does an
-// FP64 batch in which a shape's two routes round differently, so that an FP64
-// field does not depend on the rest of its batch.
+//   8 of 96x96x64 with 8 of 512x32x32 (512 planes, 53 %), FP64: 184 -> 199
+// Few planes of less than 2048 values are level either way and stay, and so do
+// the planes of a batch in which a shape's two routes round differently: the
+// route of such a shape is its own plan's (64x64x40 with 256x256x40, FP32 +
+// refinement, pays for that with 219 us against 198).
 void settle_planes(std::vector<Group> &groups)
 {
     long planes = 0;
@@ -743,7 +743,7 @@ void settle_planes(std::vector<Group> &groups)
         held += n * (double)g.N;
         planes += (long)g.d.nz * (long)g.members.size();
         values = std::max(values, g.M * g.d.ny);
-        apart = apart || (g.d.precision == POISSON_FP64 && plane_rounds_apart(g.d.nx, g.d.ny));
+        apart = apart || plane_rounds_apart(internal_prec(g.d.precision), g.d.nx, g.d.ny);
     }
     if (!separate || apart) return;
     if (3.0 * held >= all && (planes >= 512 || values < 2048)) return;

@@ -358,12 +358,17 @@ int launch_y(int prec, const YArgs &a, hipStream_t s);
 // x and y together, one workgroup per plane (periodic x and y, plain input):
 // planes that fit a workgroup's LDS only.  The forward pass writes one
 // partial record per plane.  plane_pays: such a plane fits, and a launch over
-// `planes` of them takes no longer than the separate passes.
-bool plane_pays(int prec, int nx, int ny, long planes);
-// FP64 planes whose two routes differ in their roundings (all others give the
-// same bits): rows of 32, where the compiler contracts the split's products
-// differently, and 24x384, whose y passes have another radix order
-inline bool plane_rounds_apart(int nx, int ny) { return nx == 32 || (nx == 24 && ny == 384); }
+// nz planes of each of n problems takes no longer than the separate passes.
+bool plane_pays(int prec, int nx, int ny, int nz, long n);
+// Planes whose two routes differ in their roundings: the compiler contracts the
+// products of some row lengths differently (FP64: 32; FP32: all but 96, 128 and
+// 192), and 24x384 has another radix order along y.  Their route must not depend
+// on the rest of a batch: a problem's field is that of its own plan.
+inline bool plane_rounds_apart(int prec, int nx, int ny)
+{
+    if (prec == P_F32) return nx != 96 && nx != 128 && nx != 192;
+    return nx == 32 || (nx == 24 && ny == 384);
+}
 int launch_plane_fwd(int prec, const PlaneFwd &a, hipStream_t s);
 int launch_plane_inv(int prec, const PlaneInv &a, hipStream_t s);
 int launch_plane_fwd_list(int prec, const PlaneFwd *a, int n, hipStream_t s);

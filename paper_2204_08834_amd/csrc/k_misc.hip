@@ -39,12 +39,12 @@ int launch_plane_fwd_list_f32(const PlaneFwd *, int, hipStream_t);
 int launch_plane_fwd_list_f64(const PlaneFwd *, int, hipStream_t);
 int launch_plane_inv_list_f32(const PlaneInv *, int, hipStream_t);
 int launch_plane_inv_list_f64(const PlaneInv *, int, hipStream_t);
-bool plane_pays_f32(int, int, long);
-bool plane_pays_f64(int, int, long);
+bool plane_pays_f32(int, int, int, long);
+bool plane_pays_f64(int, int, int, long);
 
-bool plane_pays(int prec, int nx, int ny, long planes)
+bool plane_pays(int prec, int nx, int ny, int nz, long n)
 {
-    return prec == P_F32 ? plane_pays_f32(nx, ny, planes) : plane_pays_f64(nx, ny, planes);
+    return prec == P_F32 ? plane_pays_f32(nx, ny, nz, n) : plane_pays_f64(nx, ny, nz, n);
 }
 int launch_plane_fwd(int prec, const PlaneFwd &a, hipStream_t s)
 {

@@ -687,18 +687,19 @@ using namespace PK_NS;
 //     128x128 12 29 -> 31, 48 0.98x
 //   FP64, 6144 values: 0.92x to 1.09x below 24 planes, 0.77x to 0.85x from 96;
 //   smaller planes: 0.63x to 1.00x at every count (FP32 to 0.92x).
-// 32x512 in FP64 is level from one plane on and stays here at every count: it is
-// the one such shape whose two routes round differently, and an FP64 field must
-// not depend on how many other problems its batch holds.  (FP32 fields of a
-// batch and of a single plan agree to FP32 rounding where their routes differ.)
-bool PK_SUFFIX(plane_pays)(int nx, int ny, long planes)
+// 32x512 in FP64 is level from one plane on and has no line.  Where the routes
+// round differently (plane_rounds_apart) the planes of one problem count, else
+// those of all problems of the shape.
+bool PK_SUFFIX(plane_pays)(int nx, int ny, int nz, long n)
 {
     int nt = 0;
     size_t lds = 0;
     if (!plane_shape(nx, ny, nt, lds)) return false;
+    constexpr int prec = sizeof(R) == 4 ? P_F32 : P_F64;
     const int values = nx / 2 * ny;
-    if (sizeof(R) == 4) return planes >= (pl_ept(values) == 16 ? 64 : 1);
-    return planes >= (values > 6144 && !plane_rounds_apart(nx, ny) ? 48 : 1);
+    const long planes = plane_rounds_apart(prec, nx, ny) ? nz : nz * n;
+    if (prec == P_F32) return planes >= (pl_ept(values) == 16 ? 64 : 1);
+    return planes >= (values > 6144 && nx != 32 ? 48 : 1);
 }
 
 #define PK_CASE_PF(N) \

@@ -227,7 +227,7 @@ def test_zero_mode_block_keeps_tiles_on_their_dies(monkeypatch):
     assert best[NEU] <= 1.25 * best[DIR], best
 
 
-def test_mixed_batches_of_few_planes_take_separate_passes(orc):
+def test_mixed_batches_of_few_planes_take_separate_passes():
     """Plane groups beside others, fewer than 512 planes or less than a third of
     the points: every shape takes the separate passes, with the FP64 fields of the
     single plans bitwise.  512 planes of a third of the points, few planes of few
@@ -240,57 +240,83 @@ def test_mixed_batches_of_few_planes_take_separate_passes(orc):
 
     other = (256, 256, 4)
     for shapes, precision, planes in (
-            ([(64, 64, 40), other], "fp64", 0), ([(64, 64, 40), other], "fp32_refine", 0),
+            ([(64, 64, 40), other], "fp64", 0), ([(64, 64, 40), other], "fp32_refine", 1),
+            ([(96, 64, 40), other], "fp32_refine", 0), ([(96, 64, 40), (64, 64, 9), other], "fp32", 2),
             ([(64, 64, 128)] * 4 + [other], "fp64", 1), ([(64, 64, 127)] * 4 + [other], "fp64", 0),
             ([(64, 64, 128)] * 4 + [(256, 256, 70)], "fp64", 0),
             ([(64, 48, 9), (24, 24, 5), (256, 256, 1)], "fp64", 0),
             ([(64, 48, 14), (24, 24, 5), (256, 256, 1)], "fp64", 2),
             ([(64, 64, 9), (48, 24, 9)], "fp64", 2),
             ([(64, 64, 9), (32, 16, 4), other], "fp64", 2),
-            ([(64, 64, 9), (32, 16, 4), other], "fp32", 0)):
+            ([(64, 64, 9), (32, 16, 4), other], "fp32", 2)):
         bp = batch(shapes, precision)
         assert bp.describe().count(" xy=plane ") == planes, (shapes, precision, bp.describe())
         bp.close()
-    for precision in ("fp64", "fp32_refine"):
-        shapes = [(64, 64, 40), (128, 96, 7), other]
+    for precision in ("fp64", "fp32", "fp32_refine"):
+        shapes = [(96, 64, 40), (128, 96, 7), other]
         print(f"[routes] mixed batch {precision}", flush=True)
-        fs = [inputs.random_rhs(*s, seed=70 + i) for i, s in enumerate(shapes)]
-        rhs = [torch.from_numpy(f).cuda() for f in fs]
+        rhs = [torch.from_numpy(inputs.random_rhs(*s, seed=70 + i)).cuda()
+               for i, s in enumerate(shapes)]
         outs = [torch.full_like(r, float("nan")) for r in rhs]
         bp = batch(shapes, precision)
+        assert bp.describe().count(" xy=plane ") == 0
         bp.solve(rhs, outs)
         torch.cuda.synchronize()
         bp.close()
-        for s, f, r, o in zip(shapes, fs, rhs, outs):
-            h = (1.0 / s[0],) * 3
-            if precision == "fp32_refine":
-                res, _ = orc.residual(f, o.cpu().numpy(), *h, NEU)
-                assert res <= 1e-10, (s, res)
-                continue
-            with P.Plan(*s, *h, NEU, precision) as plan:
+        for s, r, o in zip(shapes, rhs, outs):
+            with P.Plan(*s, *((1.0 / s[0],) * 3), NEU, precision) as plan:
+                assert (" xy=plane " in plan.describe()) == (s != other)
                 q, _ = plan.solve(r, torch.full_like(r, float("nan")))
                 torch.cuda.synchronize()
-            assert torch.equal(q, o), s
+            if precision == "fp32_refine":
+                assert float((q - o).abs().max()) <= 1e-14 * float(q.abs().max()), s
+            else:
+                assert torch.equal(q, o), (s, precision)
 
 
-@pytest.mark.parametrize("nx", [24, 32, 48, 64, 96, 128, 192, 256])
-def test_fp64_routes_give_the_same_bits(nx):
-    """Plane passes against separate ones (which per-pass timing runs), every
-    plane size of FP64: the same bits but for rows of 32 and for 24x384, whose
-    routes the plan never mixes."""
+def test_large_fp32_planes_keep_the_route_of_their_own_plan():
+    """256x128 (16 values per thread, two routes that round differently): 32
+    planes are separate in a single plan and so in a batch of four; 192x96, whose
+    routes give the same bits, goes by the planes of the batch."""
     P = _gpu()
+    for nx, ny, nz, route in ((256, 128, 32, "separate"), (192, 96, 32, "plane")):
+        spec = dict(nx=nx, ny=ny, nz=nz, dx=1.0 / nx, dy=1.0 / nx, dz=1.0 / nx, bc_z=NEU)
+        print(f"[routes] four of {nx}x{ny}x{nz} fp32", flush=True)
+        rhs = [torch.from_numpy(inputs.random_rhs(nx, ny, nz, seed=50 + i)).cuda() for i in range(4)]
+        outs = [torch.full_like(r, float("nan")) for r in rhs]
+        bp = P.BatchPlan([spec] * 4, "fp32")
+        assert f" xy={route} " in bp.describe()
+        bp.solve(rhs, outs)
+        torch.cuda.synchronize()
+        bp.close()
+        with P.Plan(**spec, precision="fp32") as plan:
+            assert " xy=separate " in plan.describe()
+            for r, o in zip(rhs, outs):
+                q, _ = plan.solve(r, torch.full_like(r, float("nan")))
+                torch.cuda.synchronize()
+                assert torch.equal(q, o)
+
+
+@pytest.mark.parametrize("precision,nx", [("fp64", n) for n in (24, 32, 48, 64, 96, 128, 192, 256)]
+                         + [("fp32", n) for n in (96, 128, 192)])
+def test_routes_give_the_same_bits(precision, nx):
+    """Plane passes against separate ones (which per-pass timing runs), every
+    plane size of FP64 and the FP32 row lengths whose route a batch may choose: the
+    same bits but for FP64 rows of 32 and 24x384, whose routes are never mixed."""
+    P = _gpu()
+    cap, many = (8192, 6144) if precision == "fp64" else (16384, 8192)
     for ny in (2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512):
-        if nx // 2 * ny > 8192:
+        if nx // 2 * ny > cap:
             continue
-        nz = 48 if nx // 2 * ny > 6144 else 3
+        nz = 64 if nx // 2 * ny > many else 3
         f = torch.from_numpy(inputs.random_rhs(nx, ny, nz, seed=ny)).cuda()
-        with P.Plan(nx, ny, nz, 1.0 / nx, 1.0 / ny, 1.0 / nz, NEU, "fp64") as plan:
-            assert " xy=plane " in plan.describe()
+        with P.Plan(nx, ny, nz, 1.0 / nx, 1.0 / ny, 1.0 / nz, NEU, precision) as plan:
+            assert " xy=plane " in plan.describe(), (nx, ny, nz)
             a, _ = plan.solve(f, torch.full_like(f, float("nan")))
             plan.set_timing(True)
             b, _ = plan.solve(f, torch.full_like(f, float("nan")))
             torch.cuda.synchronize()
-        if nx == 32 or (nx, ny) == (24, 384):
+        if precision == "fp64" and (nx == 32 or (nx, ny) == (24, 384)):
             assert torch.allclose(a, b, rtol=0, atol=1e-12 * float(b.abs().max())), (nx, ny)
         else:
             assert torch.equal(a, b), (nx, ny)
